@@ -13,8 +13,9 @@ plain 64-bit evaluation of the method (Kaehler & Wagner, "A fluctuating
 lattice-Boltzmann method with improved Galilean invariance") that shares no
 code with the library.
 
-Results of an FP32-shifted lattice that are fields (structure factors) are
-kept as float32, the precision they are computed in.
+Statistics of an FP32-shifted lattice (correlators, structure factors) are
+kept as float32: they carry the rounding of its single-precision updates
+(1e-8 to 5e-7 of the 64-bit values).
 """
 from __future__ import annotations
 
@@ -195,6 +196,10 @@ class _DeviceArray:
                                          "data": (ptr, False), "version": 3}
 
 
+def _kept(case, a) -> np.ndarray:
+    return np.asarray(a, np.float64 if case.get("precision") == "fp64" else np.float32)
+
+
 def _device_state(L, case) -> torch.Tensor:
     ptr, nbytes, _ = L.population_buffer()
     es = 4 if case["precision"] == "fp32" else 8
@@ -241,17 +246,16 @@ def run(state):
         E = state["E"]
         E.step(case["steps"])
         cs = [E.covariance(i) for i in range(case["n"])]
-        return {k: np.stack([c[k] for c in cs]) for k in _COV}
+        return {k: _kept(case, [c[k] for c in cs]) for k in _COV}
     if kind == "lattice":
         L = state["L"]
         L.step(case["steps"])
         out = {}
         if case["sample_every"]:
             c = L.covariance()
-            out.update({k: c[k] for k in _COV})
+            out.update({k: _kept(case, c[k]) for k in _COV})
         if case["sk_every"]:
-            t = np.float32 if case["precision"] == "fp32" else np.float64
-            out["sk"] = np.stack([L.structure_factor(w).astype(t, copy=False) for w in range(5)])
+            out["sk"] = _kept(case, [L.structure_factor(w) for w in range(5)])
         else:
             out["f"] = L.populations()
         return out
@@ -270,12 +274,13 @@ def run(state):
             S.submit(p, n, tag=k)
         S.drain()
         res = sorted(S.poll(len(state["requests"])), key=lambda r: r["tag"])
-        return {k: np.stack([r["cov"][k] for r in res]) for k in _COV}
+        return {k: _kept(case, [r["cov"][k] for r in res]) for k in _COV}
     L = state["L3"]
     L.step(case["steps"])
-    out = {k: v for k, v in L.covariance().items() if k not in ("nsamples", "nblocks")}
+    out = {k: _kept(case, v) for k, v in L.covariance().items()
+           if k not in ("nsamples", "nblocks")}
     if case["populations"]:
-        out["f"] = L.populations()
+        out["f"] = _kept(case, L.populations())
     return out
 
 
@@ -448,12 +453,17 @@ class _Plain:
                 nn = torch.cat([M.normals(s, tag, self.seed), M.normals(s, tag | 1, self.seed)])
                 self.f[:, i0:i0 + self.CHUNK] += torch.sqrt(self.mu * self.f0) * nn[:M.q]
         self.blocks, self.open, self.sk, self.nsk = [], None, None, 0
+        self.block_len, self.max_blocks = kw.get("block_steps", 0), 1024
 
     def sample(self):
         h = self.f - self.f0
         S = torch.cat([h.sum(1), (h @ h.T.contiguous()).reshape(-1)])
         self.open = [S, 1] if self.open is None else [self.open[0] + S, self.open[1] + 1]
-        if self.kw.get("block_steps") and self.open[1] == self.kw["block_steps"]:
+        if self.block_len and self.open[1] == self.block_len:
+            if len(self.blocks) == self.max_blocks:  # full: neighbours merge, blocks double
+                b = self.blocks
+                self.blocks = [[x[0] + y[0], x[1] + y[1]] for x, y in zip(b[::2], b[1::2])]
+                self.block_len *= 2
             self.blocks.append(self.open)
             self.open = None
 
@@ -540,6 +550,7 @@ def exact(case, seed):
         M, cs = _Method(2), []
         for side, n, kw in reqs:
             P = _Plain(M, (side, side), kw, "fnorm", (kw["ux0"], 0.0), kw["tau"])
+            P.max_blocks = 64  # the server keeps fewer
             P.step(n)
             cs.append(P.correlators())
         return {k: np.stack([c[k] for c in cs]) for k in _COV}
