@@ -129,7 +129,7 @@ struct Lattice3 {
     const size_t rec = p.sample_every > 0 ? (size_t)kMaxBlocks * kNStat3 : 0;
     const size_t sizes[] = {sizeof(Desc3), sizeof(uint64_t), sizeof(int),
                             sizeof(unsigned long long), 19 * N * es, part * sizeof(double),
-                            rec * sizeof(double), kNStat3 * sizeof(double)};
+                            rec * sizeof(double), (size_t)(1 + kFoldRows) * kNStat3 * sizeof(double)};
     size_t total = 0;
     for (size_t b : sizes) total += up(b);
     hipError_t e = hipMalloc((void**)&dev, total);
@@ -271,7 +271,7 @@ struct Lattice3 {
     std::vector<double> rec(nb * kNStat3), open(kNStat3);
     if (nb) HIPC(hipMemcpy(rec.data(), d_records, rec.size() * sizeof(double),
                            hipMemcpyDeviceToHost));
-    HIPC(launch_open_sum3(h.partials, h.ntiles, d_open, st));
+    HIPC(launch_open_sum3(h.partials, h.ntiles, d_open, d_open + kNStat3, st));
     HIPC(hipStreamSynchronize(st));
     HIPC(hipMemcpy(open.data(), d_open, kNStat3 * sizeof(double), hipMemcpyDeviceToHost));
     std::vector<double> tot(open);

@@ -656,8 +656,9 @@ hipError_t launch_merge_blocks3(double* rec, int nhalf, hipStream_t st) {
   hipLaunchKernelGGL(merge_blocks3_kernel, dim3(1), dim3(256), 0, st, rec, nhalf);
   return hipGetLastError();
 }
-hipError_t launch_open_sum3(const double* partials, int ntiles, double* out, hipStream_t st) {
-  return open_sums<kNStat3>(partials, ntiles, out, st);
+hipError_t launch_open_sum3(const double* partials, int ntiles, double* out, double* folds,
+                            hipStream_t st) {
+  return open_sums<kNStat3>(partials, ntiles, out, folds, st);
 }
 hipError_t launch_fill3(double* p, size_t n, hipStream_t st) {
   if (n == 0) return hipSuccess;

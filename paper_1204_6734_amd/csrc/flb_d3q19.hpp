@@ -32,7 +32,8 @@ hipError_t launch_io3(int storage, void* pop, double* f, const Desc3& d, int odd
                       hipStream_t st);
 hipError_t launch_close_block3(double* partials, int ntiles, double* record, hipStream_t st);
 hipError_t launch_merge_blocks3(double* rec, int nhalf, hipStream_t st);
-hipError_t launch_open_sum3(const double* partials, int ntiles, double* out, hipStream_t st);
+hipError_t launch_open_sum3(const double* partials, int ntiles, double* out, double* folds,
+                            hipStream_t st);
 hipError_t launch_fill3(double* p, size_t n, hipStream_t st);
 
 }  // namespace d3q19

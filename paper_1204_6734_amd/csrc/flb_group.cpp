@@ -32,7 +32,7 @@ void Group::layout(Arena& a) {
   d_clock = a.take<uint64_t>(1);
   d_err = a.take<int>(n);
   d_err_step = a.take<unsigned long long>(n);
-  d_open = a.take<double>(kNStat);
+  d_open = a.take<double>((size_t)(1 + kFoldRows) * kNStat);
   d_B = a.take<double>(81);
   d_mode = a.take<double2>(kModeBlocks);
   d_close = a.take<double*>(2 * (size_t)n);
@@ -555,7 +555,7 @@ int Group::read_covariance(int s, flb_cov* out) {
   std::vector<double> rec;
   double open[kNStat] = {0};
   if (d_partials[s]) {
-    HIPC(launch_open_sum(d_partials[s], hdesc[s].ntiles, d_open, st));
+    HIPC(launch_open_sum(d_partials[s], hdesc[s].ntiles, d_open, d_open + kNStat, st));
     HIPC(hipMemcpyAsync(open, d_open, sizeof(open), hipMemcpyDeviceToHost, st));
     rec.resize((size_t)std::max<uint64_t>(stats[s].nb, 1) * kNStat);
     if (stats[s].nb > 0)

@@ -625,8 +625,9 @@ hipError_t launch_merge_blocks(double* rec, int nhalf, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_open_sum(const double* partials, int ntiles, double* out, hipStream_t st) {
-  return open_sums<kNStat>(partials, ntiles, out, st);
+hipError_t launch_open_sum(const double* partials, int ntiles, double* out, double* folds,
+                           hipStream_t st) {
+  return open_sums<kNStat>(partials, ntiles, out, folds, st);
 }
 
 hipError_t launch_fill(double* p, size_t n, double v, hipStream_t st) {

@@ -14,6 +14,7 @@ constexpr int kWideTileMinNx = 256;  // rows this long use 256 x 1 tiles (else 6
 constexpr int kMaxTilesPerBlock = 4;  // workgroups of up to 1024 threads
 constexpr int kMaxBlock = kBlock * kMaxTilesPerBlock;
 constexpr int kNStat = 54;   // 9 first moments + 45 unique second moments
+constexpr int kFoldRows = 256;  // ranges of tiles whose sums are folded, then added in order
 constexpr int kMaxTimeBlocks = 1024;
 constexpr int kMaxDirectDft = 4096;  // longest row transformed by the O(n^2) DFT
 enum : int { kErrInvalidVelocity = 1, kErrNonFinite = 2 };

@@ -31,8 +31,9 @@ struct ScratchHead {
 };
 constexpr size_t kPartialsOffset = 4096;
 static_assert(sizeof(ScratchHead) <= kPartialsOffset, "descriptor block fits");
-constexpr size_t kScratchBytes =
+constexpr size_t kFoldsOffset =
     kPartialsOffset + (size_t)FLB_NOALLOC_MAX_TILES * kNStat * sizeof(double);
+constexpr size_t kScratchBytes = kFoldsOffset + (size_t)kFoldRows * kNStat * sizeof(double);
 constexpr int kMaxDevices = 64;
 
 // One per device, held by the code object for the life of the process.
@@ -147,7 +148,8 @@ extern "C" int flb_step_noalloc(const flb_params* p, void* pop, uint64_t t0, uin
     done += chunk;
   }
   if (sampling) {
-    e = launch_open_sum(partials, d.ntiles, sums, st);
+    e = launch_open_sum(partials, d.ntiles, sums,
+                        reinterpret_cast<double*>(base + kFoldsOffset), st);
     if (e != hipSuccess) return hip_fail(e, "sums");
   }
   if (status) {

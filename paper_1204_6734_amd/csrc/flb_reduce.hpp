@@ -7,6 +7,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
+#include "flb_kernels.hpp"
+
 namespace flb {
 
 // Thread layout (v, j): v = statistic (padded to VP), j = one of J lanes
@@ -44,19 +48,51 @@ __device__ __forceinline__ void fold_tiles(double* partials, int ntiles, int chu
   }
 }
 
-// Stage two: record = the folded rows summed in range order; rows cleared.
+// Ranges of stage one: at most kFoldRows workgroups of at least one tile.
+inline void fold_ranges(int ntiles, int* chunk, int* nranges) {
+  const int c = ntiles > kFoldRows ? (ntiles + kFoldRows - 1) / kFoldRows : 1;
+  *chunk = c;
+  *nranges = (ntiles + c - 1) / c;
+}
+
+// Stage two: the folded rows (row b at folds + b stride) summed in range
+// order, thread v its statistic.  The chain of additions is short (256 FP64
+// additions, ~1 us); what bounds it is the latency of the loads, so they are
+// issued kGatherBatch at a time before the additions that use them.  One
+// load per addition took 41 us for 256 ranges of 54 statistics and 66 us for
+// 209 (MI355X, kernel trace); batched, the same additions in the same order
+// take 10 and 20 us (64 loads at a time spilled registers: 13 and 68 us).
+constexpr int kGatherBatch = 32;
+template <int NSTAT>
+__device__ __forceinline__ double sum_folds(const double* folds, int nranges, size_t stride) {
+  const int v = threadIdx.x;
+  double s = 0.0;
+  for (int b0 = 0; b0 < nranges; b0 += kGatherBatch) {
+    double x[kGatherBatch];
+    // past the end the last row is read again and not added
+#pragma unroll
+    for (int k = 0; k < kGatherBatch; ++k)
+      x[k] = folds[(size_t)min(b0 + k, nranges - 1) * stride + v];
+#pragma unroll
+    for (int k = 0; k < kGatherBatch; ++k)
+      if (b0 + k < nranges) s += x[k];
+  }
+  return s;
+}
+
+// Stage two of closing a block: record = the folded rows' sum, by the first
+// threads of one workgroup; then all its threads clear the rows (one
+// wavefront clearing 256 rows held the kernel at 14 us).
 template <int NSTAT>
 __device__ __forceinline__ void gather_folds(double* partials, int nranges, int chunk,
                                              double* record) {
-  const int v = threadIdx.x;
-  if (v >= NSTAT) return;
-  double s = 0.0;
-  for (int b = 0; b < nranges; ++b) {
-    double* q = partials + (size_t)b * chunk * NSTAT + v;
-    s += *q;
-    *q = 0.0;
-  }
-  record[v] = s;
+  constexpr int VP = SumShape<NSTAT>::VP, J = SumShape<NSTAT>::J;
+  const int v = threadIdx.x % VP, j = threadIdx.x / VP;
+  const size_t stride = (size_t)chunk * NSTAT;
+  if (j == 0 && v < NSTAT) record[v] = sum_folds<NSTAT>(partials, nranges, stride);
+  __syncthreads();
+  if (v < NSTAT)
+    for (int b = j; b < nranges; b += J) partials[b * stride + v] = 0.0;
 }
 
 template <int NSTAT>
@@ -66,7 +102,7 @@ __global__ __launch_bounds__(1024) void fold_tiles_kernel(double* partials, int 
 }
 
 template <int NSTAT>
-__global__ void gather_folds_kernel(double* partials, int nranges, int chunk, double* record) {
+__global__ __launch_bounds__(1024) void gather_folds_kernel(double* partials, int nranges, int chunk, double* record) {
   gather_folds<NSTAT>(partials, nranges, chunk, record);
 }
 
@@ -79,36 +115,36 @@ __global__ __launch_bounds__(1024) void fold_tiles_many_kernel(double* const* pa
 }
 
 template <int NSTAT>
-__global__ void gather_folds_many_kernel(double* const* partials, int nranges, int chunk,
+__global__ __launch_bounds__(1024) void gather_folds_many_kernel(double* const* partials, int nranges, int chunk,
                                          double* const* records, size_t record_offset) {
   gather_folds<NSTAT>(partials[blockIdx.y], nranges, chunk, records[blockIdx.y] + record_offset);
 }
 
-// Open sums (partials left as they are): one workgroup, lanes as above.
+// Open sums (partials left as they are): workgroup b sums tiles
+// [b chunk, min((b+1) chunk, n)) into row b of out, lanes as above.
 template <int NSTAT>
-__global__ __launch_bounds__(1024) void open_sums_kernel(const double* partials, int ntiles,
-                                                         double* out) {
+__global__ __launch_bounds__(1024) void open_folds_kernel(const double* partials, int ntiles,
+                                                          int chunk, double* out) {
   constexpr int VP = SumShape<NSTAT>::VP, J = SumShape<NSTAT>::J;
   __shared__ double red[J][VP];
   const int v = threadIdx.x % VP, j = threadIdx.x / VP;
+  const int t0 = blockIdx.x * chunk, t1 = min(t0 + chunk, ntiles);
   double s = 0.0;
   if (v < NSTAT)
-    for (int t = j; t < ntiles; t += J) s += partials[(size_t)t * NSTAT + v];
+    for (int t = t0 + j; t < t1; t += J) s += partials[(size_t)t * NSTAT + v];
   red[j][v] = s;
   __syncthreads();
   if (j == 0 && v < NSTAT) {
     double tot = red[0][v];
 #pragma unroll
     for (int k = 1; k < J; ++k) tot += red[k][v];
-    out[v] = tot;
+    out[(size_t)blockIdx.x * NSTAT + v] = tot;
   }
 }
 
-// Ranges of stage one: at most 256 workgroups of at least one tile.
-inline void fold_ranges(int ntiles, int* chunk, int* nranges) {
-  const int c = ntiles > 256 ? (ntiles + 255) / 256 : 1;
-  *chunk = c;
-  *nranges = (ntiles + c - 1) / c;
+template <int NSTAT>
+__global__ void open_gather_kernel(const double* folds, int nranges, double* out) {
+  if (threadIdx.x < NSTAT) out[threadIdx.x] = sum_folds<NSTAT>(folds, nranges, NSTAT);
 }
 
 // record[NSTAT] = sum of the partials over all tiles; partials cleared.
@@ -121,7 +157,7 @@ hipError_t close_block_sums(double* partials, int ntiles, double* record, hipStr
                      ntiles, chunk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gather_folds_kernel<NSTAT>, dim3(1), dim3(SumShape<NSTAT>::VP), 0, st,
+  hipLaunchKernelGGL(gather_folds_kernel<NSTAT>, dim3(1), dim3(1024), 0, st,
                      partials, nranges, chunk, record);
   return hipGetLastError();
 }
@@ -139,16 +175,35 @@ hipError_t close_block_sums_many(double* const* partials, double* const* records
                      partials, ntiles, chunk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gather_folds_many_kernel<NSTAT>, dim3(1, n), dim3(SumShape<NSTAT>::VP), 0,
+  hipLaunchKernelGGL(gather_folds_many_kernel<NSTAT>, dim3(1, n), dim3(1024), 0,
                      st, partials, nranges, chunk, records, record_offset);
   return hipGetLastError();
 }
 
-// out[NSTAT] = sum of the partials over all tiles (partials unchanged).
+// out[NSTAT] = sum of the partials over all tiles (partials unchanged);
+// folds: kFoldRows rows of scratch.  Few tiles are summed by one workgroup in
+// one launch; above kOpenOneBlock tiles a single workgroup's walk over the
+// partials is far below the memory's rate (65536 tiles of 209 statistics,
+// 110 MB: 7.2 ms, 15 GB/s), so ranges of tiles go to up to 256 workgroups and
+// a second launch adds the ranges in order (0.05 ms).
+constexpr int kOpenOneBlock = 64;
 template <int NSTAT>
-hipError_t open_sums(const double* partials, int ntiles, double* out, hipStream_t st) {
+hipError_t open_sums(const double* partials, int ntiles, double* out, double* folds,
+                     hipStream_t st) {
   if (ntiles <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(open_sums_kernel<NSTAT>, dim3(1), dim3(1024), 0, st, partials, ntiles, out);
+  if (ntiles <= kOpenOneBlock) {
+    hipLaunchKernelGGL(open_folds_kernel<NSTAT>, dim3(1), dim3(1024), 0, st, partials, ntiles,
+                       ntiles, out);
+    return hipGetLastError();
+  }
+  const int chunk = std::max(16, (ntiles + kFoldRows - 1) / kFoldRows);
+  const int nranges = (ntiles + chunk - 1) / chunk;
+  hipLaunchKernelGGL(open_folds_kernel<NSTAT>, dim3(nranges), dim3(1024), 0, st, partials, ntiles,
+                     chunk, folds);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(open_gather_kernel<NSTAT>, dim3(1), dim3(SumShape<NSTAT>::VP), 0, st, folds,
+                     nranges, out);
   return hipGetLastError();
 }
 

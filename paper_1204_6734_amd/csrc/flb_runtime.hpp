@@ -82,7 +82,9 @@ hipError_t launch_close_block(double* partials, int ntiles, double* record, hipS
 hipError_t launch_close_block_many(double* const* partials, double* const* records,
                                   size_t record_offset, int n, int ntiles, hipStream_t st);
 hipError_t launch_merge_blocks(double* rec, int nhalf, hipStream_t st);
-hipError_t launch_open_sum(const double* partials, int ntiles, double* out, hipStream_t st);
+// folds: kFoldRows rows of kNStat doubles of scratch
+hipError_t launch_open_sum(const double* partials, int ntiles, double* out, double* folds,
+                           hipStream_t st);
 hipError_t launch_fill(double* p, size_t n, double v, hipStream_t st);
 hipError_t launch_stream_copy(const void* in, void* out, size_t n4, hipStream_t st);
 hipError_t launch_stream_probe(int storage, void* pop, int nx, int ny, uint32_t pitch, int wide,

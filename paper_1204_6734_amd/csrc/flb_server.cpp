@@ -233,7 +233,7 @@ int flb_server::finish(const Active& a) {
                    : FLB_OK;
   if (a.desc.partials && !err) {
     double* rec = records_of(a, arena, cfg.precision);
-    HIPC(launch_open_sum(a.desc.partials, a.desc.ntiles, d_open, st));
+    HIPC(launch_open_sum(a.desc.partials, a.desc.ntiles, d_open, d_open + kNStat, st));
     double open[kNStat];
     std::vector<double> recs((size_t)std::max<uint64_t>(a.stats.nb, 1) * kNStat);
     HIPC(hipMemcpyAsync(open, d_open, sizeof(open), hipMemcpyDeviceToHost, st));
@@ -392,7 +392,7 @@ int flb_server_create(const flb_server_config* cfg, void* hip_stream, flb_server
     if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "slot tables"));
   }
   e = hipMalloc((void**)&S->d_clock, 8);
-  if (e == hipSuccess) e = hipMalloc((void**)&S->d_open, kNStat * sizeof(double));
+  if (e == hipSuccess) e = hipMalloc((void**)&S->d_open, (size_t)(1 + kFoldRows) * kNStat * sizeof(double));
   if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "clock"));
   e = hipMemsetAsync(S->d_clock, 0, 8, S->st);
   if (e == hipSuccess) e = hipStreamSynchronize(S->st);
