@@ -582,11 +582,11 @@ __device__ __forceinline__ void scaled_noise(const SiteDraw<R, NOISE32>& D, R rh
 }
 
 // One collision, eq. (6), on shifted populations h (in place), with the
-// site's Gaussian draw (read only when the lattice has noise).  Returns
-// error bits; on error h is left unchanged.
-template <typename R, int BASIS, bool NOISE32>
-__device__ __forceinline__ int collide(R h[9], const CollideConst<R>& C,
-                                       const SiteDraw<R, NOISE32>& draw) {
+// site's Gaussian draw (a SiteDraw, or what scaled_noise takes in its place;
+// read only when the lattice has noise).  Returns error bits; on error h is
+// left unchanged.
+template <typename R, int BASIS, typename Draw>
+__device__ __forceinline__ int collide(R h[9], const CollideConst<R>& C, const Draw& draw) {
   LocalState<R> S;
   if (!local_state(h, C.rho0, C.ux0, C.uy0, S)) return kErrNonFinite;
   const R ux = S.ux, uy = S.uy;

@@ -25,7 +25,7 @@ static size_t storage_size(int storage) { return storage == 0 ? sizeof(double) :
 
 // Lay out every device array of the group in `a` (a.base may be null to
 // size it).
-void Group::layout(Arena& a) {
+void Group::layout(Arena& a, bool second) {
   const int n = (int)P.size();
   d_slots = a.take<SlotDesc>(n);
   d_prefix = a.take<int>(n + 2);
@@ -65,6 +65,14 @@ void Group::layout(Arena& a) {
     d_twx = a.take<char>(P[0].nx * cplx);
     d_twy = a.take<char>(P[0].ny * cplx);
   }
+  // the several-step kernel's second population buffer, all slots together
+  pop2 = nullptr;
+  if (second)
+    for (int s = 0; s < n; ++s) {
+      char* p = a.take<char>(population_elems(P[s].nx, P[s].ny) * storage_size(storage));
+      if (s == 0) pop2 = p;
+      hdesc[s].pop2 = p;
+    }
 }
 
 int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t dev_bytes) {
@@ -104,9 +112,16 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     prefix[s + 1] = prefix[s] + hdesc[s].ntiles;
   }
   total_tiles = prefix[n];
+  hipDeviceProp_t prop;
+  int dev_id = 0;
+  HIPC(hipGetDevice(&dev_id));
+  HIPC(hipGetDeviceProperties(&prop, dev_id));
+  max_lds = prop.sharedMemPerBlock;
+  device = dev_id;
   Arena sizing;
   layout(sizing);
   need_bytes = sizing.used + 256;
+  bool second = false;
   if (dev_buf) {
     if (dev_bytes < need_bytes)
       return set_error(FLB_E_ARG, "device buffer too small: %zu < %zu bytes", dev_bytes,
@@ -114,7 +129,23 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     dev = dev_buf;
     own_mem = false;
   } else {
-    hipError_t e = hipMalloc(&dev, need_bytes);
+    hipError_t e = hipErrorOutOfMemory;
+    plan_multi(prop.multiProcessorCount);
+    if (multi_max) {
+      Arena both;
+      layout(both, true);
+      second = take_second(both.used + 256 - need_bytes);
+      if (second) e = hipMalloc(&dev, both.used + 256);
+      if (second && e != hipSuccess) {
+        (void)hipGetLastError();
+        second = false;  // one step per launch needs less
+      }
+      if (second) need_bytes = both.used + 256;
+    }
+    if (!second) {
+      multi_max = 0;
+      e = hipMalloc(&dev, need_bytes);
+    }
     if (e != hipSuccess) {
       dev = nullptr;
       return set_error(FLB_E_OOM, "hipMalloc(%zu): %s", need_bytes, hipGetErrorString(e));
@@ -123,7 +154,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
   }
   Arena a;
   a.base = (char*)(((uintptr_t)dev + 255) & ~(uintptr_t)255);
-  layout(a);
+  layout(a, second);
   if (stream) {
     st = (hipStream_t)stream;
     own_stream = false;
@@ -131,12 +162,6 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     HIPC(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     own_stream = true;
   }
-  hipDeviceProp_t prop;
-  int dev_id = 0;
-  HIPC(hipGetDevice(&dev_id));
-  HIPC(hipGetDeviceProperties(&prop, dev_id));
-  max_lds = prop.sharedMemPerBlock;
-  device = dev_id;
   if (d_skacc && (!sk_transform_supported(P[0].nx, storage, max_lds) ||
                   !sk_transform_supported(P[0].ny, storage, max_lds)))
     return set_error(FLB_E_ARG,
@@ -144,6 +169,9 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
                      "%d (FP32) or at most %d",
                      (int)(max_lds / sizeof(double2)), (int)(max_lds / sizeof(float2)),
                      kMaxDirectDft);
+  if (multi_max)
+    for (int c = 0; c < nclass; ++c) 
+      HIPC(multi_prepare(storage, ccompute[c], basis, P[0].nx, multi_max, max_lds));
   launch = tuned_launch(*this);
   // per-slot pointers and measurement bases
   mt0.assign(n, std::vector<double>(81));
@@ -303,19 +331,21 @@ hipError_t Group::launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c) 
   return hipSuccess;
 }
 
-int Group::launch_one(uint32_t k, bool sample, int odd) {
+// fn() enqueues `steps` steps; with profiling on, between two events.
+template <typename Fn>
+int Group::profiled(Fn fn, uint64_t steps) {
   if (profiling) {
     std::pair<hipEvent_t, hipEvent_t> ev;
     HIPC(hipEventCreate(&ev.first));
     HIPC(hipEventCreate(&ev.second));
     HIPC(hipEventRecord(ev.first, st));
-    HIPC(launch_classes(k, sample, odd, launch));
+    HIPC(fn());
     HIPC(hipEventRecord(ev.second, st));
     events.push_back(ev);
-    prof_launches += 1;
+    prof_launches += steps;
     return FLB_OK;
   }
-  HIPC(launch_classes(k, sample, odd, launch));
+  HIPC(fn());
   return FLB_OK;
 }
 
@@ -332,24 +362,136 @@ bool Group::graph_friendly() const {
   return true;
 }
 
-// Steps from time t until (and including) the step whose sample closes a
-// time block of some slot; replays must not straddle such a step.
-uint64_t Group::steps_to_close() const {
+// Steps from time tt (up to which the samples are counted) until (and
+// including) the first step after tt + skip whose sample closes a time block
+// of some slot; replays and several-step launches must not straddle one.
+uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
   uint64_t m = ~0ull;
   for (int s = 0; s < (int)P.size(); ++s) {
-    const uint64_t se = (uint64_t)P[s].sample_every;
-    if (se == 0 || stats[s].tb_len == 0) continue;
-    const uint64_t left = stats[s].tb_len - stats[s].tb_fill;  // samples to the close
-    const uint64_t first = (t + se - 1) / se * se;              // next sampled time
-    m = std::min(m, first + (left - 1) * se - t + 1);
+    const uint64_t se = (uint64_t)P[s].sample_every, len = stats[s].tb_len;
+    if (se == 0 || len == 0) continue;
+    const uint64_t left = len - stats[s].tb_fill;       // samples to the close
+    const uint64_t first = (tt + se - 1) / se * se;     // next sampled time
+    uint64_t r = first + (left - 1) * se - tt + 1;
+    while (r <= skip) r += len * se;
+    m = std::min(m, r);
   }
   return m;
+}
+
+// ------------------------------------------------- several steps per launch
+// Tiles per workgroup for every number of steps a launch may take.  Several
+// steps pay while a step is held by latency, that is while the chip is not
+// full: at one tile per workgroup (the halo is cheapest to recompute when
+// nothing else wants the SIMDs; two tiles measured slower), up to one
+// workgroup per CU.  Measured (us a step, one step per launch -> this; without
+// / with sums of every step): FP32 21^2 2.9 -> 1.8 / 4.0 -> 2.2, 64^2 2.9 ->
+// 2.3 / 4.1 -> 2.9, 256^2 (256 tiles) 3.2 -> 2.8 / 4.1 -> 3.4, but 256 x 320
+// (320 tiles) 3.6 -> 4.7 / 4.7 -> 6.3.  Lattices of two or more rows per
+// wavefront have short workgroups, two of which share a CU (64 x 21^2, 384
+// tiles: 3.8 -> 2.3 / 4.8 -> 3.1), and take six steps as well as four.  FP64
+// collisions gain on those only (21^2 3.7 -> 2.5 / 4.9 -> 3.5, 32^2 3.6 -> 3.1
+// / 4.9 -> 4.2; 64^2 3.7 -> 3.9 / 4.9 -> 5.5): their halo costs more than the
+// launches saved.
+void Group::plan_multi(int cus) {
+  multi_max = 0;
+  std::fill(&multi_nt[0][0], &multi_nt[0][0] + 2 * (kMultiMaxSteps + 1), 0);
+  const int nx = P[0].nx;
+  const bool narrow = nx <= kTileX / 2;
+  if (hdesc[0].wide || (compute == 0 && !narrow)) return;
+  if (total_tiles > (narrow && compute == 1 ? 2 * cus : cus)) return;
+  const int most = narrow && compute == 1 && total_tiles <= cus ? 6 : 4;
+  for (int sample = 0; sample < 2; ++sample)
+    for (int K = 2; K <= most; K += 2)
+      if (multi_fits(storage, compute, sample != 0, nx, K, 1, max_lds)) {
+        multi_nt[sample][K] = 1;
+        multi_max = std::max(multi_max, K);
+      }
+}
+
+// Whether a second population buffer of this size is taken: small ones
+// always, larger ones when they leave the caller most of the free memory.
+bool Group::take_second(size_t bytes) const {
+  if (bytes <= ((size_t)256 << 20)) return true;
+  size_t freeb = 0, total = 0;
+  if (hipMemGetInfo(&freeb, &total) != hipSuccess) return false;
+  return bytes <= freeb / 8;
+}
+
+// Largest launch from the even time tt within `lim` steps that holds no
+// structure-factor step but its first.
+int Group::pass_steps(uint64_t tt, uint64_t lim) const {
+  for (int s = 0; s < (int)P.size(); ++s)
+    if (d_skacc && P[s].sk_every > 0)
+      lim = std::min(lim, (uint64_t)P[s].sk_every - tt % (uint64_t)P[s].sk_every);
+  for (int K = multi_max; K >= 2; K -= 2)
+    if ((uint64_t)K <= lim && multi_nt[pass_samples(tt, K)][K]) return K;
+  return 0;
+}
+
+// Whether a launch of K steps from time tt takes the variant with sums.
+bool Group::pass_samples(uint64_t tt, int K) const {
+  for (int s = 0; s < (int)P.size(); ++s) {
+    const uint64_t se = (uint64_t)P[s].sample_every;
+    if (sk_due(s, tt) || (se > 0 && (tt + se - 1) / se * se < tt + (uint64_t)K)) return true;
+  }
+  return false;
+}
+
+// The next two launches of several steps from time tt (pop -> pop2 -> pop:
+// outside a pair the state is always in the first buffer), within `left`
+// steps and with time blocks closing after a launch at most.  kb = 0: none.
+void Group::pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb) const {
+  *ka = *kb = 0;
+  if (!multi_max || forced_launch || (tt & 1)) return;
+  const uint64_t m = closes ? steps_to_close(tt, 0) : ~0ull;
+  for (int K = pass_steps(tt, std::min(left, m)); K >= 2; K -= 2) {
+    if (!multi_nt[pass_samples(tt, K)][K]) continue;
+    const uint64_t m2 = closes ? steps_to_close(tt, (uint64_t)K) - (uint64_t)K : ~0ull;
+    *ka = K;
+    *kb = pass_steps(tt + (uint64_t)K, std::min(left - (uint64_t)K, m2));
+    if (*kb) return;
+  }
+}
+
+// One launch of K steps from time tt (step index k of the device clock).
+hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
+  const bool sample = pass_samples(tt, K);
+  for (int i = 0; i < nclass; ++i) {
+    const hipError_t e =
+        launch_step_multi(storage, ccompute[i], basis, sample, d_slots + cfirst[i], ccount[i],
+                          P[0].nx, P[0].ny, K, multi_nt[sample][K], flip, d_clock, k, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+int Group::abandon_capture(hipError_t e) {
+  hipGraph_t g = nullptr;
+  (void)hipStreamEndCapture(st, &g);
+  if (g) (void)hipGraphDestroy(g);
+  return hip_fail(e, "capture step");
 }
 
 int Group::capture_graph() {
   if (graph_exec) return FLB_OK;
   HIPC(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   for (int k = 0; k < graph_chunk; ++k) {
+    int pass[2];
+    pass_pair((uint64_t)k, (uint64_t)(graph_chunk - k), false, &pass[0], &pass[1]);
+    if (pass[1]) {
+      hipError_t e = hipSuccess;
+      for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+        e = launch_pass((uint32_t)k, (uint64_t)k, pass[i], i);
+        if (e == hipSuccess && sk_due(0, (uint64_t)k))
+          e = launch_sk_sample(storage, d_z, d_zt, d_skacc, P[0].nx, P[0].ny, d_twx, d_twy,
+                               max_lds, st);
+        k += pass[i];
+      }
+      if (e != hipSuccess) return abandon_capture(e);
+      --k;  // the loop's own step
+      continue;
+    }
     // replays start at multiples of graph_chunk (even), so step k of a chunk
     // has parity k & 1 and a slot samples there iff k is a multiple of its
     // interval; a structure-factor step also takes the sampling variant (it
@@ -362,12 +504,7 @@ int Group::capture_graph() {
       if (sk_due(s, (uint64_t)k))
         e = launch_sk_sample(storage, d_z, d_zt, d_skacc, P[s].nx, P[s].ny, d_twx, d_twy,
                              max_lds, st);
-    if (e != hipSuccess) {
-      hipGraph_t g;
-      (void)hipStreamEndCapture(st, &g);
-      if (g) (void)hipGraphDestroy(g);
-      return hip_fail(e, "capture step");
-    }
+    if (e != hipSuccess) return abandon_capture(e);
   }
   HIPC(launch_tick(d_clock, (uint64_t)graph_chunk, st));
   HIPC(hipStreamEndCapture(st, &graph));
@@ -382,7 +519,7 @@ int Group::step(uint64_t nsteps) {
   uint64_t done = 0;
   while (done < nsteps) {
     const uint64_t left = nsteps - done;
-    if (use_graph && left >= K && t % K == 0 && steps_to_close() >= K) {
+    if (use_graph && left >= K && t % K == 0 && steps_to_close(t, 0) >= K) {
       int rc = capture_graph();
       if (rc != FLB_OK) return rc;
       if (profiling) {
@@ -411,13 +548,27 @@ int Group::step(uint64_t nsteps) {
     uint64_t chunk = std::min<uint64_t>(left, 1ull << 30);
     if (use_graph) {
       const uint64_t to_align = t % K == 0 ? K : K - t % K;
-      chunk = std::min(chunk, std::min(to_align, std::max<uint64_t>(1, steps_to_close())));
+      chunk = std::min(chunk, std::min(to_align, std::max<uint64_t>(1, steps_to_close(t, 0))));
     }
     for (uint64_t k = 0; k < chunk; ++k) {
       const uint64_t tt = t + k;
+      int pass[2];
+      pass_pair(tt, chunk - k, true, &pass[0], &pass[1]);
+      if (pass[1]) {
+        for (int i = 0; i < 2; ++i) {
+          int rc = profiled([&] { return launch_pass((uint32_t)k, t + k, pass[i], i); },
+                            (uint64_t)pass[i]);
+          for (int j = 0; j < pass[i] && rc == FLB_OK; ++j) rc = after_step(t + k + (uint64_t)j);
+          if (rc != FLB_OK) return rc;
+          k += (uint64_t)pass[i];
+        }
+        --k;  // the loop's own step
+        continue;
+      }
       bool sample = false;
       for (int s = 0; s < n; ++s) sample |= sample_due(s, tt) || sk_due(s, tt);
-      int rc = launch_one((uint32_t)k, sample, (int)(tt & 1));
+      int rc = profiled(
+          [&] { return launch_classes((uint32_t)k, sample, (int)(tt & 1), launch); }, 1);
       if (rc != FLB_OK) return rc;
       rc = after_step(tt);
       if (rc != FLB_OK) return rc;

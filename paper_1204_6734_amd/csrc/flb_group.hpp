@@ -9,6 +9,7 @@
 
 #include "flb.h"
 #include "flb_kernels.hpp"
+#include "flb_multi.hpp"
 #include "flb_runtime.hpp"
 
 namespace flb {
@@ -59,9 +60,17 @@ struct Group {
   int64_t err_step_host = -1;
   std::vector<Stats> stats;
   std::vector<std::vector<double>> mt0;
-  // launch shape of the step kernel
+  // launch shape of the one-step kernel; a shape the caller forced is used
+  // for every step
   LaunchCfg launch;
+  bool forced_launch = false;
   int device = 0;
+  // several steps per launch: the second population buffer (null: one step
+  // per launch) and, without and with correlator sums, the tiles per workgroup
+  // for each number of steps (0: not taken)
+  char* pop2 = nullptr;
+  int multi_nt[2][kMultiMaxSteps + 1] = {{0}};
+  int multi_max = 0;
   // graphs
   int graph_chunk = 0;
   hipGraph_t graph = nullptr;
@@ -77,16 +86,24 @@ struct Group {
   Group& operator=(const Group&) = delete;
   ~Group();
 
-  void layout(Arena& a);
+  void layout(Arena& a, bool second = false);
   int init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t dev_bytes);
   bool sample_due(int s, uint64_t tt) const;
   bool sk_due(int s, uint64_t tt) const;
   int after_step(uint64_t tt, bool replayed = false);
   bool lockstep_close(uint64_t tt) const;
-  int launch_one(uint32_t k, bool sample, int odd);
+  template <typename Fn>
+  int profiled(Fn fn, uint64_t steps);
   hipError_t launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c);
   bool graph_friendly() const;
-  uint64_t steps_to_close() const;
+  uint64_t steps_to_close(uint64_t tt, uint64_t skip) const;
+  int abandon_capture(hipError_t e);
+  void plan_multi(int cus);
+  bool take_second(size_t bytes) const;
+  int pass_steps(uint64_t tt, uint64_t lim) const;
+  bool pass_samples(uint64_t tt, int K) const;
+  void pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb) const;
+  hipError_t launch_pass(uint32_t k, uint64_t tt, int K, int flip);
   int capture_graph();
   int step(uint64_t nsteps);
   int sync();

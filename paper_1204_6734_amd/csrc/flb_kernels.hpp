@@ -10,7 +10,11 @@ namespace flb {
 constexpr int kTileX = 64;   // sites of one wavefront: 64 consecutive sites of a row
 constexpr int kTileY = 4;    // four wavefronts per 256-site tile
 constexpr int kBlock = kTileX * kTileY;
-constexpr int kWideTileMinNx = 256;  // rows this long use 256 x 1 tiles (else 64 x 4)
+// Rows of at least kWideTileMinNx sites use 256 x 1 tiles (else 64 x 4), in FP32
+// storage on lattices of more than kWideTileMinSites sites: smaller ones take
+// several steps per launch and need tiles with little halo.
+constexpr int kWideTileMinNx = 256;
+constexpr uint64_t kWideTileMinSites = 1u << 16;
 constexpr int kMaxTilesPerBlock = 4;  // workgroups of up to 1024 threads
 constexpr int kMaxBlock = kBlock * kMaxTilesPerBlock;
 constexpr int kNStat = 54;   // 9 first moments + 45 unique second moments
@@ -53,6 +57,7 @@ struct SlotDesc {
   double shift[9];      // f_i^0(rho0, u0): storage holds h = f - shift
   float rho0f, ux0f, uy0f, xc2f;  // single-precision copies
   float rtf[6], xcf[6], shiftf[9];
+  void* pop2;           // second buffer of the several-step kernel, or null
 };
 
 // Whether t is a multiple of m (m >= 1; magic, shift for m from magic_div):

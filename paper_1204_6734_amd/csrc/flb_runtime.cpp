@@ -158,9 +158,21 @@ size_t population_elems(int nx, int ny) { return (size_t)9 * ny * row_pitch(nx);
 
 // Tile shape and count: 256 x 1 tiles (four wavefronts along a row) on rows
 // of at least kWideTileMinNx sites, whose wavefronts then read longer
-// stretches of one row (measured faster), else 64 x 4.
-void tile_shape(int nx, int ny, int* wide, int* tiles_x, int* ntiles) {
-  *wide = nx >= kWideTileMinNx ? 1 : 0;
+// stretches of one row (measured faster on large lattices), else 64 x 4.
+// Also 64 x 4 where the order of the correlator sums may change by a rounding
+// of FP64 (FP32 storage, or no sums at all) and
+//  - the lattice is small enough for several steps per launch, which need
+//    tiles with little halo (kWideTileMinSites), or
+//  - the last tile of a row is mostly empty: the wavefronts without sites hold
+//    their workgroup's slots (64 lattices of 300 x 200, eight wavefronts a
+//    row for five of sites: FP32 57 -> 45 us a step, FP64 130 -> 103).
+void tile_shape(const flb_params& p, int* wide, int* tiles_x, int* ntiles) {
+  const int nx = p.nx, ny = p.ny;
+  const int64_t quarters = (nx + kTileX - 1) / kTileX;
+  const int64_t padded = (quarters + kTileY - 1) / kTileY * kTileY;
+  const bool free_order = p.precision == FLB_FP32_SHIFTED || p.sample_every == 0;
+  const bool small = p.precision == FLB_FP32_SHIFTED && (uint64_t)nx * ny <= kWideTileMinSites;
+  *wide = nx >= kWideTileMinNx && !small && !(free_order && 10 * padded > 11 * quarters) ? 1 : 0;
   const int tw = *wide ? kTileX * kTileY : kTileX, th = *wide ? 1 : kTileY;
   *tiles_x = (nx + tw - 1) / tw;
   *ntiles = *tiles_x * ((ny + th - 1) / th);
@@ -183,7 +195,7 @@ void fill_slot(const flb_params* p, SlotDesc* d) {
   d->nx = p->nx;
   d->ny = p->ny;
   d->pitch = row_pitch(p->nx);
-  tile_shape(p->nx, p->ny, &d->wide, &d->tiles_x, &d->ntiles);
+  tile_shape(*p, &d->wide, &d->tiles_x, &d->ntiles);
   magic_div((uint32_t)d->tiles_x, &d->tx_magic, &d->tx_shift);
   magic_div(p->sample_every > 0 ? (uint32_t)p->sample_every : 1u, &d->se_magic, &d->se_shift);
   magic_div(p->sk_every > 0 ? (uint32_t)p->sk_every : 1u, &d->sk_magic, &d->sk_shift);
@@ -395,7 +407,7 @@ extern "C" int flb_copy_probe(int32_t nx, int32_t ny, int32_t precision, int32_t
   const int storage = precision == FLB_FP64 ? 0 : 1;
   const size_t bytes = flb::population_elems(nx, ny) * (storage == 0 ? 8 : 4);
   int wide = 0, tiles_x = 0, ntiles = 0;
-  flb::tile_shape(nx, ny, &wide, &tiles_x, &ntiles);
+  flb::tile_shape(p, &wide, &tiles_x, &ntiles);
   const uint32_t pitch = flb::row_pitch(nx);
   void* a = nullptr;
   if (hipMalloc(&a, bytes) != hipSuccess) return set_error(FLB_E_OOM, "copy probe");

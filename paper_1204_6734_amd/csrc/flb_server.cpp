@@ -98,7 +98,7 @@ struct Active {
 
 static size_t request_bytes_of(const flb_params& p, int storage) {
   int wide = 0, tiles_x = 0, ntiles = 0;
-  tile_shape(p.nx, p.ny, &wide, &tiles_x, &ntiles);
+  tile_shape(p, &wide, &tiles_x, &ntiles);
   size_t b = population_elems(p.nx, p.ny) * (storage == 0 ? 8 : 4);
   b = (b + 255) & ~(size_t)255;
   if (p.sample_every > 0) {

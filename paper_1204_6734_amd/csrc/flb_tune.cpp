@@ -84,6 +84,7 @@ int Group::set_launch(const flb_launch_config* c) {
   HIPC(hipStreamSynchronize(st));
   drop_graph();
   launch = LaunchCfg{c->tiles_per_block, c->grid_blocks};
+  forced_launch = true;
   return FLB_OK;
 }
 
@@ -195,6 +196,7 @@ int Group::autotune(int reps, flb_launch_config* results, int max_results, int* 
                      return a.ms_per_step < b.ms_per_step;
                    });
   drop_graph();
+  forced_launch = false;
   launch = LaunchCfg{meas[0].tiles_per_block, meas[0].grid_blocks};
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
