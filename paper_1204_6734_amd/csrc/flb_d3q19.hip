@@ -245,6 +245,25 @@ __device__ __forceinline__ int collide3_hermite(R h[19], const Const3<R>& C, int
   return 0;
 }
 
+// Which projections of the rows 4..18 on the conserved rows can be other than
+// zero: the second-order rows on 1, and fewer on sqrt3 (v_a - u_a).  255 of the
+// 480 products P_i P_j of the Schur complement remain; without fast-math the
+// compiler keeps a product with a zero, so it has to be told.
+struct ProjectionPattern {
+  bool one[15], vel[3][15];
+};
+constexpr ProjectionPattern projection_pattern() {
+  ProjectionPattern p{};
+  for (int i = 0; i < 15; ++i)
+    for (int k = 0; k < 9; ++k) {
+      if (kPi3[4 + i][k] != 0.0) p.one[i] = true;
+      for (int a = 0; a < 3; ++a)
+        if (kPi3[4 + i][k] != 0.0 || kG3[1 + a][4 + i][k] != 0.0) p.vel[a][i] = true;
+    }
+  return p;
+}
+constexpr ProjectionPattern kProj = projection_pattern();
+
 constexpr int kBlock3 = 256;   // threads per workgroup (one 64 x 4 tile)
 // The factor L of the Schur complement G' = <m^a, m^b>_g - P0 P0^T -
 // sum_a P_a P_a^T, one column at a time (packed lower part L[i(i+1)/2 + k]),
@@ -273,9 +292,10 @@ __device__ __forceinline__ void factor_relax(const R mono[9], R uu, const R P0[1
 #pragma unroll
       for (int k = 0; k < 9; ++k)
         if (kG3[4 + i][4 + j][k] != 0.0) G += R(kG3[4 + i][4 + j][k]) * mono[k];
-      G = fma(-P0[i], P0[j], G);
+      if (kProj.one[i] && kProj.one[j]) G = fma(-P0[i], P0[j], G);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) G = fma(-P[c][i], P[c][j], G);
+      for (int c = 0; c < 3; ++c)
+        if (kProj.vel[c][i] && kProj.vel[c][j]) G = fma(-P[c][i], P[c][j], G);
 #pragma unroll
       for (int k = 0; k < j; ++k) G -= L[i * (i + 1) / 2 + k] * L[j * (j + 1) / 2 + k];
       L[i * (i + 1) / 2 + j] = G;
