@@ -55,6 +55,7 @@ struct Lattice3 {
   flb3_params p{};
   int storage = 1;
   size_t N = 0;
+  int cus = 256;
   Desc3 h{};
   Desc3* d_desc = nullptr;
   char* dev = nullptr;
@@ -155,6 +156,9 @@ struct Lattice3 {
     d_open = (double*)q;
     h.err = d_err;
     h.err_step = d_err_step;
+    int dev_id = 0;
+    HIPC(hipGetDevice(&dev_id));
+    HIPC(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id));
     if (stream) {
       st = (hipStream_t)stream;
     } else {
@@ -212,7 +216,7 @@ struct Lattice3 {
           HIPC(hipEventRecord(ev.first, st));
         }
         HIPC(launch_step3(storage, p.basis == FLB_BASIS_HERMITE ? 1 : 0, h.one_tau != 0, sample,
-                          (int)(tt & 1), h.ntiles, d_desc, d_clock, (uint32_t)k, st));
+                          (int)(tt & 1), h.ntiles, cus, d_desc, d_clock, (uint32_t)k, st));
         if (profiling) {
           HIPC(hipEventRecord(ev.second, st));
           events.push_back(ev);

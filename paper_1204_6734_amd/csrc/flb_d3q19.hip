@@ -419,12 +419,17 @@ __device__ __forceinline__ int stat_pair(int i, int j) {
 // tile's partials; the whole workgroup calls this.  For one wavefront they
 // are the entries of X^T X, X the 64 x 20 matrix of the nineteen df_i and a
 // constant 1 per site, split into column blocks X0 (df_0..df_15) and X1
-// (df_16..df_18, the constant, zeros): X0^T X0, X0^T X1 and X1^T X1 take
-// sixteen FP64 matrix instructions each (16 x 16 output, four sites per
-// instruction), on values the wavefront stages in LDS; lane l reads column
-// l % 16 of site l / 16 of each group of four and holds output row
-// l / 16 + 4 r, column l % 16 in element r.  The four wavefronts then add
-// their sums in a fixed order.
+// (df_16..df_18 and the constant).  Four sites at a time, on values the
+// wavefront stages in LDS, X0^T X0 takes one v_mfma_f64_16x16x4 (64 cycles of
+// the matrix pipe), and X0^T X1 and X1^T X1, whose 16 x 4 and 4 x 4 results
+// would leave most of such a product empty, one v_mfma_f64_4x4x4 each (four
+// blocks: rows 4 b .. 4 b + 3 of X0; only block 0 of X1^T X1 is used), with
+// the sums in the same order.  (256^3 FP32: a step with sums 1.33 -> 1.13 ms;
+// 48 products of 16x16x4 took 3072 cycles a wavefront.)
+// Operands: lane l holds column l % 16 (X0) or l % 4 (X1) of site l / 16 of
+// the four.  Results: 16x16x4 row l / 16 + 4 r, column l % 16 in element r;
+// 4x4x4 row l / 16 of block l / 4 % 4, column l % 4.  The four wavefronts then
+// add their sums in a fixed order.
 template <typename S, typename R>
 __device__ __forceinline__ void sample3(const R h[19], bool active, double* partials) {
   __shared__ S xs[4][64 * 19];
@@ -440,30 +445,34 @@ __device__ __forceinline__ void sample3(const R h[19], bool active, double* part
   // accesses complete in program order
   __builtin_amdgcn_wave_barrier();
   const int col = lane & 15, grp = lane >> 4;
-  const int c1 = col < 3 ? 16 + col : 18;  // in-range column of block 1
-  const double pad1 = col == 3 ? 1.0 : 0.0;
-  double4_v3 a00 = {0.0, 0.0, 0.0, 0.0}, a01 = a00, a11 = a00;
+  const int j1 = lane & 3, b1 = (lane >> 2) & 3;
+  const int c1 = j1 < 3 ? 16 + j1 : 18;  // in-range column of block 1
+  double4_v3 a00 = {0.0, 0.0, 0.0, 0.0};
+  double a01 = 0.0, a11 = 0.0;
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const S* row = x + (4 * q + grp) * 19;
     const double v0 = (double)row[col];
     const S r1 = row[c1];
-    const double v1 = col < 3 ? (double)r1 : pad1;
+    const double v1 = j1 < 3 ? (double)r1 : 1.0;
     a00 = __builtin_amdgcn_mfma_f64_16x16x4f64(v0, v0, a00, 0, 0, 0);
-    a01 = __builtin_amdgcn_mfma_f64_16x16x4f64(v0, v1, a01, 0, 0, 0);
-    a11 = __builtin_amdgcn_mfma_f64_16x16x4f64(v1, v1, a11, 0, 0, 0);
+    a01 = __builtin_amdgcn_mfma_f64_4x4x4f64(v0, v1, a01, 0, 0, 0);
+    a11 = __builtin_amdgcn_mfma_f64_4x4x4f64(v1, v1, a11, 0, 0, 0);
   }
   double* rw = red[wave];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = grp + 4 * r;  // output row, 0..15
     if (i <= col) rw[stat_pair(i, col)] = a00[r];
-    if (col < 3) rw[stat_pair(i, 16 + col)] = a01[r];
-    if (col == 3) rw[i] = a01[r];  // sum of df_i
   }
-  if (grp < 3) {  // rows 16..18 of block 1 (element 0 of lanes 0..47)
-    if (col < 3 && grp <= col) rw[stat_pair(16 + grp, 16 + col)] = a11[0];
-    if (col == 3) rw[16 + grp] = a11[0];
+  {
+    const int i = 4 * b1 + grp;  // row of X0
+    if (j1 < 3) rw[stat_pair(i, 16 + j1)] = a01;
+    else rw[i] = a01;  // sum of df_i
+  }
+  if (b1 == 0 && grp < 3) {  // rows 16..18
+    if (j1 < 3 && grp <= j1) rw[stat_pair(16 + grp, 16 + j1)] = a11;
+    if (j1 == 3) rw[16 + grp] = a11;
   }
   __syncthreads();
   if (adds)
@@ -478,12 +487,10 @@ __device__ __forceinline__ uint32_t cell(int x, int y, int z, const Desc3& d) {
 __device__ __forceinline__ int wrap(int a, int n) { return a < 0 ? a + n : (a >= n ? a - n : a); }
 
 // Wavefronts per SIMD the register allocation of a step variant aims at:
-// three in FP32 (the one-relaxation-time f-norm collision fits in 163
-// registers; the general one spills 32-40 bytes per lane there and still
-// runs 1.5 % faster than at two), one in FP64.
+// three in FP32; in FP64 one or two (the launcher's choice, `two`).
 template <typename R>
-constexpr int waves3() {
-  return sizeof(R) == 8 ? 1 : 3;
+constexpr int waves3(bool two) {
+  return sizeof(R) == 8 ? (two ? 2 : 1) : 3;
 }
 
 // One 64 x 4 tile of one z plane per workgroup, one wavefront per tile row,
@@ -492,8 +499,8 @@ constexpr int waves3() {
 // per-lane part of an offset is one of three columns x - 1, x, x + 1; the
 // row part (nine distinct (y, z) shifts) is scalar.  Tiles are renumbered
 // so that each XCD sweeps a contiguous range of z planes.
-template <typename S, typename R, int BASIS, bool SAMPLE, int ODD, bool ONE>
-__global__ __launch_bounds__(kBlock3) __attribute__((amdgpu_waves_per_eu(waves3<R>()))) void
+template <typename S, typename R, int BASIS, bool SAMPLE, int ODD, bool ONE, bool TWO>
+__global__ __launch_bounds__(kBlock3) __attribute__((amdgpu_waves_per_eu(waves3<R>(TWO)))) void
 step3_kernel(const Desc3* __restrict__ desc, const uint64_t* __restrict__ clock,
              uint32_t step_idx) {
   const Desc3& d = *desc;
@@ -626,36 +633,48 @@ __global__ void fill3_kernel(double* p, size_t n) {
 }
 
 // ------------------------------------------------------------- launchers
-template <typename S, typename R, int BASIS, bool ONE>
+template <typename S, int BASIS, bool ONE, bool TWO>
 static hipError_t step3_t(bool sample, int odd, int ntiles, const Desc3* d,
                           const uint64_t* clock, uint32_t k, hipStream_t st) {
   const dim3 g(ntiles), b(kBlock3);
+#define FLB_STEP3(SMP, ODD) \
+  hipLaunchKernelGGL((step3_kernel<S, S, BASIS, SMP, ODD, ONE, TWO>), g, b, 0, st, d, clock, k)
   if (sample) {
-    if (odd)
-      hipLaunchKernelGGL((step3_kernel<S, R, BASIS, true, 1, ONE>), g, b, 0, st, d, clock, k);
-    else
-      hipLaunchKernelGGL((step3_kernel<S, R, BASIS, true, 0, ONE>), g, b, 0, st, d, clock, k);
+    if (odd) FLB_STEP3(true, 1);
+    else FLB_STEP3(true, 0);
   } else {
-    if (odd)
-      hipLaunchKernelGGL((step3_kernel<S, R, BASIS, false, 1, ONE>), g, b, 0, st, d, clock, k);
-    else
-      hipLaunchKernelGGL((step3_kernel<S, R, BASIS, false, 0, ONE>), g, b, 0, st, d, clock, k);
+    if (odd) FLB_STEP3(false, 1);
+    else FLB_STEP3(false, 0);
   }
+#undef FLB_STEP3
   return hipGetLastError();
 }
 
-template <typename S>
+template <typename S, bool TWO>
 static hipError_t step3_s(int basis, bool one_tau, bool sample, int odd, int ntiles,
                           const Desc3* d, const uint64_t* clock, uint32_t k, hipStream_t st) {
-  if (basis == 1) return step3_t<S, S, 1, false>(sample, odd, ntiles, d, clock, k, st);
-  if (one_tau) return step3_t<S, S, 0, true>(sample, odd, ntiles, d, clock, k, st);
-  return step3_t<S, S, 0, false>(sample, odd, ntiles, d, clock, k, st);
+  if (basis == 1) return step3_t<S, 1, false, TWO>(sample, odd, ntiles, d, clock, k, st);
+  if (one_tau) return step3_t<S, 0, true, TWO>(sample, odd, ntiles, d, clock, k, st);
+  return step3_t<S, 0, false, TWO>(sample, odd, ntiles, d, clock, k, st);
 }
 
+// FP64 collisions take 256 registers and more.  Two wavefronts per SIMD (some
+// spills) hide the latencies of the factorisation and let two workgroups share
+// a CU; one is faster while there is at most one workgroup per CU, and for
+// mixed relaxation times without sums, which spill most.  Measured (us a step,
+// one -> two wavefronts; tiles; one relaxation time / with sums / mixed /
+// mixed with sums): 216 tiles 9.4 -> 10.5 / 12.1 -> 13.4 / 10.1 -> 11.6 / 12.9
+// -> 14.5; 270 16.4 -> 14.8 / 22.2 -> 19.2 / 17.8 -> 17.4 / 23.4 -> 21.6; 1500
+// 47.9 -> 41.7 / 66.0 -> 54.4 / 52.8 -> 49.9 / 69.8 -> 61.3; 4096 122.6 -> 117.1
+// / 168.5 -> 146.7 / 132.3 -> 139.0 / 178.0 -> 165.3.
 hipError_t launch_step3(int storage, int basis, bool one_tau, bool sample, int odd, int ntiles,
-                        const Desc3* d, const uint64_t* clock, uint32_t k, hipStream_t st) {
-  if (storage == 0) return step3_s<double>(basis, one_tau, sample, odd, ntiles, d, clock, k, st);
-  return step3_s<float>(basis, one_tau, sample, odd, ntiles, d, clock, k, st);
+                        int cus, const Desc3* d, const uint64_t* clock, uint32_t k,
+                        hipStream_t st) {
+  if (storage != 0)
+    return step3_s<float, false>(basis, one_tau, sample, odd, ntiles, d, clock, k, st);
+  if (basis == 0 && ntiles > cus && (one_tau || sample))
+    return step3_s<double, true>(basis, one_tau, sample, odd, ntiles, d, clock, k, st);
+  return step3_s<double, false>(basis, one_tau, sample, odd, ntiles, d, clock, k, st);
 }
 
 hipError_t launch_io3(int storage, void* pop, double* f, const Desc3& d, int odd, int to_storage,

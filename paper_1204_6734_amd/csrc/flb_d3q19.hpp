@@ -26,8 +26,9 @@ struct Desc3 {
   float rho0f, u0f[3], rtf[15], xcf[15], xc2f;  // the same in FP32
 };
 
+// cus: the device's compute units
 hipError_t launch_step3(int storage, int basis, bool one_tau, bool sample, int odd, int ntiles,
-                        const Desc3* d, const uint64_t* clock, uint32_t k, hipStream_t st);
+                        int cus, const Desc3* d, const uint64_t* clock, uint32_t k, hipStream_t st);
 hipError_t launch_io3(int storage, void* pop, double* f, const Desc3& d, int odd, int to_storage,
                       hipStream_t st);
 hipError_t launch_close_block3(double* partials, int ntiles, double* record, hipStream_t st);
