@@ -239,12 +239,18 @@ def make_params(nx, ny, rho0=1.0, ux0=0.0, uy0=0.0, kT=0.0, tau=(1.0,) * 6, seed
     return p
 
 
+def _values(c, name: str, n: int) -> np.ndarray:
+    """The n doubles of a structure from field `name` on, copied once."""
+    off = getattr(type(c), name).offset
+    return np.frombuffer(c, np.float64, n, off).copy()
+
+
 def _cov_dict(c: Cov) -> dict:
-    out = {"nsamples": int(c.nsamples), "nblocks": int(c.nblocks),
-           "mean_df": np.array(c.mean_df[:])}
-    for k in ("cov_f", "cov_m_fnorm_u0", "cov_m_hermite", "se_cov_f", "se_cov_m",
-              "se_cov_m_hermite"):
-        out[k] = np.array(getattr(c, k)[:]).reshape(9, 9)
+    v = _values(c, "mean_df", 9 + 6 * 81)
+    out = {"nsamples": int(c.nsamples), "nblocks": int(c.nblocks), "mean_df": v[:9]}
+    for i, k in enumerate(("cov_f", "cov_m_fnorm_u0", "cov_m_hermite", "se_cov_f", "se_cov_m",
+                           "se_cov_m_hermite")):
+        out[k] = v[9 + 81 * i:90 + 81 * i].reshape(9, 9)
     return out
 
 
@@ -558,10 +564,9 @@ class Lattice3:
     def covariance(self) -> dict:
         c = Cov3()
         _check(load().flb3_lattice_read_covariance(self.h, C.byref(c)), "cov3")
-        return {"nsamples": int(c.nsamples), "nblocks": int(c.nblocks),
-                "mean_df": np.array(c.mean_df[:]),
-                "cov_f": np.array(c.cov_f[:]).reshape(19, 19),
-                "se_cov_f": np.array(c.se_cov_f[:]).reshape(19, 19)}
+        v = _values(c, "mean_df", 19 + 2 * 361)
+        return {"nsamples": int(c.nsamples), "nblocks": int(c.nblocks), "mean_df": v[:19],
+                "cov_f": v[19:380].reshape(19, 19), "se_cov_f": v[380:].reshape(19, 19)}
 
     def reset_stats(self):
         _check(load().flb3_lattice_reset_stats(self.h), "reset3")

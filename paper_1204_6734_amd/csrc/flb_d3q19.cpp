@@ -52,6 +52,7 @@ static int check3(const flb3_params* p) {
 }
 
 struct Lattice3 {
+  Staging staging;
   flb3_params p{};
   int storage = 1;
   size_t N = 0;
@@ -235,11 +236,17 @@ struct Lattice3 {
   }
 
   int sync() {
-    HIPC(hipStreamSynchronize(st));
+    return read_errors(nullptr, 0);
+  }
+
+  // The error flags and the given pieces, in one readout behind the work
+  // enqueued so far; an error goes before the data.
+  int read_errors(const HostPiece* more, int nmore) {
     int err = 0;
     unsigned long long es = 0;
-    HIPC(hipMemcpy(&err, d_err, sizeof(int), hipMemcpyDeviceToHost));
-    HIPC(hipMemcpy(&es, d_err_step, sizeof(es), hipMemcpyDeviceToHost));
+    HostPiece p[4] = {{&err, d_err, sizeof(err)}, {&es, d_err_step, sizeof(es)}};
+    for (int i = 0; i < nmore; ++i) p[2 + i] = more[i];
+    HIPC(copy_out(p, 2 + nmore, st));
     if (err) {
       err_step_host = (int64_t)es;
       if (err & kErrInvalidVelocity)
@@ -260,24 +267,27 @@ struct Lattice3 {
     } fr{d_f};
     if (to_storage) HIPC(hipMemcpy(d_f, f, 19 * N * sizeof(double), hipMemcpyHostToDevice));
     HIPC(launch_io3(storage, h.pop, d_f, h, (int)(t & 1), to_storage, st));
-    HIPC(hipStreamSynchronize(st));
-    if (!to_storage) HIPC(hipMemcpy(f, d_f, 19 * N * sizeof(double), hipMemcpyDeviceToHost));
+    if (to_storage) HIPC(hipStreamSynchronize(st));
+    else HIPC(copy_out(f, d_f, 19 * N * sizeof(double), st));
     return FLB_OK;
   }
 
   int read_covariance(flb3_cov* out) {
-    int rc = sync();
+    const bool any = h.partials && nsamples > 0;
+    std::vector<double> rec(nb * kNStat3), open(kNStat3);
+    HostPiece p[2];
+    int n = 0;
+    if (any) {
+      HIPC(launch_open_sum3(h.partials, h.ntiles, d_open, d_open + kNStat3, st));
+      p[n++] = {open.data(), d_open, kNStat3 * sizeof(double)};
+      if (nb) p[n++] = {rec.data(), d_records, rec.size() * sizeof(double)};
+    }
+    const int rc = read_errors(p, n);
     if (rc != FLB_OK) return rc;
     std::memset(out, 0, sizeof(*out));
     out->nsamples = nsamples;
     out->nblocks = nb;
-    if (!h.partials || nsamples == 0) return FLB_OK;
-    std::vector<double> rec(nb * kNStat3), open(kNStat3);
-    if (nb) HIPC(hipMemcpy(rec.data(), d_records, rec.size() * sizeof(double),
-                           hipMemcpyDeviceToHost));
-    HIPC(launch_open_sum3(h.partials, h.ntiles, d_open, d_open + kNStat3, st));
-    HIPC(hipStreamSynchronize(st));
-    HIPC(hipMemcpy(open.data(), d_open, kNStat3 * sizeof(double), hipMemcpyDeviceToHost));
+    if (!any) return FLB_OK;
     std::vector<double> tot(open);
     for (uint64_t b = 0; b < nb; ++b)
       for (int v = 0; v < kNStat3; ++v) tot[v] += rec[b * kNStat3 + v];

@@ -112,12 +112,11 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     prefix[s + 1] = prefix[s] + hdesc[s].ntiles;
   }
   total_tiles = prefix[n];
-  hipDeviceProp_t prop;
-  int dev_id = 0;
-  HIPC(hipGetDevice(&dev_id));
-  HIPC(hipGetDeviceProperties(&prop, dev_id));
-  max_lds = prop.sharedMemPerBlock;
-  device = dev_id;
+  int lds = 0, cus = 0;
+  HIPC(hipGetDevice(&device));
+  HIPC(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
+  HIPC(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+  max_lds = (size_t)lds;
   Arena sizing;
   layout(sizing);
   need_bytes = sizing.used + 256;
@@ -130,7 +129,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     own_mem = false;
   } else {
     hipError_t e = hipErrorOutOfMemory;
-    plan_multi(prop.multiProcessorCount);
+    plan_multi(cus);
     if (multi_max) {
       Arena both;
       layout(both, true);
@@ -581,18 +580,26 @@ int Group::step(uint64_t nsteps) {
 }
 
 int Group::sync() {
-  HIPC(hipStreamSynchronize(st));
+  // waits for the stream too
+  return read_errors(nullptr, 0);
+}
+
+// The error flags of every slot and the given pieces, in one readout behind
+// the work enqueued so far; an error goes before the data.
+int Group::read_errors(const HostPiece* more, int nmore) {
   const int n = (int)P.size();
   std::vector<int> err(n);
   std::vector<unsigned long long> es(n);
-  HIPC(hipMemcpy(err.data(), d_err, n * sizeof(int), hipMemcpyDeviceToHost));
-  HIPC(hipMemcpy(es.data(), d_err_step, n * sizeof(unsigned long long), hipMemcpyDeviceToHost));
-  int code = FLB_OK;
+  std::vector<HostPiece> all{{err.data(), d_err, n * sizeof(int)},
+                             {es.data(), d_err_step, n * sizeof(unsigned long long)}};
+  all.insert(all.end(), more, more + nmore);
+  HIPC(copy_out(all.data(), (int)all.size(), st));
   for (int s = 0; s < n; ++s) {
     err_step_host = -1;
     if (err[s]) {
       // own time of slot s at the failing step
       const int64_t stp = (int64_t)es[s];
+      int code;
       if (err[s] & kErrInvalidVelocity) {
         code = set_error(FLB_E_INVALID_VELOCITY,
                          "lattice %d: local velocity outside the validity region at step %lld",
@@ -605,7 +612,32 @@ int Group::sync() {
       return code;
     }
   }
-  return code;
+  return FLB_OK;
+}
+
+// Nine planes of `rows` rows in d_io to rows r0 .. of host planes of N values.
+int Group::copy_planes(void* dst, size_t N, size_t off, size_t B, size_t es) {
+  if (B == N) {  // the whole lattice: one piece
+    HIPC(copy_out(dst, d_io, 9 * N * es, st));
+    return FLB_OK;
+  }
+  HostPiece p[9];
+  for (int i = 0; i < 9; ++i)
+    p[i] = {(char*)dst + (i * N + off) * es, (const char*)d_io + i * B * es, B * es};
+  HIPC(copy_out(p, 9, st));
+  return FLB_OK;
+}
+
+// The other way (synchronous for pageable memory).
+int Group::copy_planes_in(const void* src, size_t N, size_t off, size_t B, size_t es) {
+  if (B == N) {
+    HIPC(hipMemcpyAsync(d_io, src, 9 * N * es, hipMemcpyHostToDevice, st));
+    return FLB_OK;
+  }
+  for (int i = 0; i < 9; ++i)
+    HIPC(hipMemcpyAsync((char*)d_io + i * B * es, (const char*)src + (i * N + off) * es, B * es,
+                        hipMemcpyHostToDevice, st));
+  return FLB_OK;
 }
 
 int Group::read_populations(int s, double* f) {
@@ -624,11 +656,8 @@ int Group::read_rows(int s, int y0, int nrows, double* f) {
     const int rows = std::min(band_rows, y0 + nrows - b0);
     HIPC(launch_read_state(storage, pop[s], hdesc[s].pitch, d_io, p.nx, p.ny, (int)(t & 1), slot_shift(hdesc[s]),
                            b0, rows, st));
-    const size_t B = (size_t)rows * p.nx;
-    for (int i = 0; i < 9; ++i)
-      HIPC(hipMemcpyAsync(f + i * N + (size_t)(b0 - y0) * p.nx, d_io + i * B, B * sizeof(double),
-                          hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
+    rc = copy_planes(f, N, (size_t)(b0 - y0) * p.nx, (size_t)rows * p.nx, sizeof(double));
+    if (rc != FLB_OK) return rc;
   }
   return FLB_OK;
 }
@@ -642,10 +671,8 @@ int Group::set_populations(int s, const double* f, uint64_t tnew) {
   HIPC(hipMemcpyAsync(d_clock, &t, sizeof(uint64_t), hipMemcpyHostToDevice, st));
   for (int y0 = 0; y0 < p.ny; y0 += band_rows) {
     const int rows = std::min(band_rows, p.ny - y0);
-    const size_t B = (size_t)rows * p.nx;
-    for (int i = 0; i < 9; ++i)
-      HIPC(hipMemcpyAsync(d_io + i * B, f + i * N + (size_t)y0 * p.nx, B * sizeof(double),
-                          hipMemcpyHostToDevice, st));
+    const int rc = copy_planes_in(f, N, (size_t)y0 * p.nx, (size_t)rows * p.nx, sizeof(double));
+    if (rc != FLB_OK) return rc;
     HIPC(launch_write_state(storage, pop[s], hdesc[s].pitch, d_io, p.nx, p.ny, (int)(t & 1), slot_shift(hdesc[s]),
                             y0, rows, st));
     HIPC(hipStreamSynchronize(st));
@@ -690,30 +717,27 @@ int Group::read_moments(int s, int at, double* m) {
     const int rows = std::min(band_rows, p.ny - y0);
     HIPC(launch_moments(storage, pop[s], hdesc[s].pitch, B, d_io, p.nx, p.ny, (int)(t & 1), p.rho0, p.ux0,
                         p.uy0, slot_shift(hdesc[s]), d_err + s, y0, rows, st));
-    const size_t Bn = (size_t)rows * p.nx;
-    for (int a = 0; a < 9; ++a)
-      HIPC(hipMemcpyAsync(m + a * N + (size_t)y0 * p.nx, d_io + a * Bn, Bn * sizeof(double),
-                          hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
+    rc = copy_planes(m, N, (size_t)y0 * p.nx, (size_t)rows * p.nx, sizeof(double));
+    if (rc != FLB_OK) return rc;
   }
   return sync();
 }
 
 int Group::read_covariance(int s, flb_cov* out) {
-  int rc = sync();
-  if (rc != FLB_OK) return rc;
   const flb_params& p = P[s];
   std::vector<double> rec;
   double open[kNStat] = {0};
+  HostPiece piece[2];
+  int n = 0;
   if (d_partials[s]) {
     HIPC(launch_open_sum(d_partials[s], hdesc[s].ntiles, d_open, d_open + kNStat, st));
-    HIPC(hipMemcpyAsync(open, d_open, sizeof(open), hipMemcpyDeviceToHost, st));
+    piece[n++] = {open, d_open, sizeof(open)};
     rec.resize((size_t)std::max<uint64_t>(stats[s].nb, 1) * kNStat);
     if (stats[s].nb > 0)
-      HIPC(hipMemcpyAsync(rec.data(), d_records[s], stats[s].nb * kNStat * sizeof(double),
-                          hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
+      piece[n++] = {rec.data(), d_records[s], stats[s].nb * kNStat * sizeof(double)};
   }
+  const int rc = read_errors(piece, n);
+  if (rc != FLB_OK) return rc;
   return finish_covariance(stats[s], rec, open, (uint64_t)p.nx * p.ny, mt0[s].data(), out);
 }
 
@@ -738,21 +762,14 @@ int Group::read_structure_factor(int which, double* out) {
   if (!d_skacc) return set_error(FLB_E_STATE, "structure factors are off (sk_every = 0)");
   if (which < 0 || which > 4) return set_error(FLB_E_ARG, "unknown structure factor %d", which);
   const int nx = P[0].nx, ny = P[0].ny;
-  const size_t H = sk_half();
-  std::vector<double> tmp(H);  // device order [kx][ky], kx <= nx/2
-  HIPC(hipMemcpy(tmp.data(), d_skacc + which * H, H * sizeof(double), hipMemcpyDeviceToHost));
   const double norm = nsk > 0 ? 1.0 / ((double)nsk * (double)nx * (double)ny) : 0.0;
-  for (int kx = 0; kx < nx; ++kx)
-    for (int ky = 0; ky < ny; ++ky) {
-      double v;
-      if (kx <= nx / 2) {
-        v = tmp[(size_t)kx * ny + ky];
-      } else {  // the value at -k: equal, or the conjugate for the cross term
-        v = tmp[(size_t)(nx - kx) * ny + (ky == 0 ? 0 : ny - ky)];
-        if (which == FLB_SK_JXJY_IM) v = -v;
-      }
-      out[(size_t)ky * nx + kx] = v * norm;
-    }
+  // d_io holds 9 band_rows rows
+  for (int k0 = 0; k0 < ny; k0 += 9 * band_rows) {
+    const int rows = std::min(9 * band_rows, ny - k0);
+    HIPC(launch_sk_expand(d_skacc + which * sk_half(), d_io, nx, ny, k0, rows, norm,
+                          which == FLB_SK_JXJY_IM, st));
+    HIPC(copy_out(out + (size_t)k0 * nx, d_io, (size_t)rows * nx * sizeof(double), st));
+  }
   return FLB_OK;
 }
 
@@ -767,9 +784,7 @@ int Group::read_fourier_mode(int which, int kx, int ky, double out[2]) {
   HIPC(launch_fourier_mode(storage, pop[0], hdesc[0].pitch, d_mode, kModeBlocks, p.nx, p.ny,
                            (int)(t & 1), which, nkx, nky, p.ux0, p.uy0, st));
   std::vector<double2> part(nblocks);
-  HIPC(hipMemcpyAsync(part.data(), d_mode, nblocks * sizeof(double2), hipMemcpyDeviceToHost,
-                      st));
-  HIPC(hipStreamSynchronize(st));
+  HIPC(copy_out(part.data(), d_mode, nblocks * sizeof(double2), st));
   double sr = 0, si = 0;
   for (auto& v : part) {
     sr += v.x;
@@ -808,12 +823,9 @@ int Group::checkpoint(void* host, size_t bytes) {
   const size_t N = (size_t)p.nx * p.ny, es = storage_size(storage);
   for (int y0 = 0; y0 < p.ny; y0 += band_rows) {
     const int rows = std::min(band_rows, p.ny - y0);
-    const size_t B = (size_t)rows * p.nx;
     HIPC(launch_raw_state(storage, pop[0], hdesc[0].pitch, d_io, p.nx, p.ny, (int)(t & 1), 1, y0, rows, st));
-    for (int i = 0; i < 9; ++i)
-      HIPC(hipMemcpyAsync(dst + (i * N + (size_t)y0 * p.nx) * es, (char*)d_io + i * B * es, B * es,
-                          hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
+    rc = copy_planes(dst, N, (size_t)y0 * p.nx, (size_t)rows * p.nx, es);
+    if (rc != FLB_OK) return rc;
   }
   return FLB_OK;
 }
@@ -837,10 +849,8 @@ int Group::restore(const void* host, size_t bytes) {
   const size_t N = (size_t)p.nx * p.ny, es = storage_size(storage);
   for (int y0 = 0; y0 < p.ny; y0 += band_rows) {
     const int rows = std::min(band_rows, p.ny - y0);
-    const size_t B = (size_t)rows * p.nx;
-    for (int i = 0; i < 9; ++i)
-      HIPC(hipMemcpyAsync((char*)d_io + i * B * es, src + (i * N + (size_t)y0 * p.nx) * es, B * es,
-                          hipMemcpyHostToDevice, st));
+    const int rc = copy_planes_in(src, N, (size_t)y0 * p.nx, (size_t)rows * p.nx, es);
+    if (rc != FLB_OK) return rc;
     HIPC(launch_raw_state(storage, pop[0], hdesc[0].pitch, d_io, p.nx, p.ny, (int)(t & 1), 0, y0, rows, st));
     HIPC(hipStreamSynchronize(st));
   }

@@ -17,6 +17,7 @@ namespace flb {
 constexpr int kModeBlocks = 1024;
 
 struct Group {
+  Staging staging;
   std::vector<flb_params> P;
   std::vector<SlotDesc> hdesc;
   std::vector<int> prefix;
@@ -107,6 +108,9 @@ struct Group {
   int capture_graph();
   int step(uint64_t nsteps);
   int sync();
+  int read_errors(const HostPiece* more, int nmore);
+  int copy_planes(void* dst, size_t N, size_t off, size_t B, size_t es);
+  int copy_planes_in(const void* src, size_t N, size_t off, size_t B, size_t es);
   int read_populations(int s, double* f);
   int read_rows(int s, int y0, int nrows, double* f);
   int set_populations(int s, const double* f, uint64_t tnew);

@@ -523,6 +523,40 @@ __global__ void sk_accumulate_kernel(const typename Cplx<T>::type* __restrict__ 
   acc[4u * H + i] += bi * cr - br * ci;  // Im(b conj c)
 }
 
+// The accumulators ([kx][ky], kx <= nx/2) as the full plane [ky][kx] times
+// norm, through 32 x 32 tiles in LDS: read along ky, written along kx.
+__global__ __launch_bounds__(256) void sk_expand_kernel(const double* __restrict__ acc,
+                                                        double* out, int nx, int ny, int ky0,
+                                                        int rows, double norm, int negate) {
+  constexpr int TILE = 32, STEP = 256 / TILE;
+  __shared__ double tile[TILE][TILE + 1];
+  const int bx = blockIdx.x * TILE, by = blockIdx.y * TILE;
+  const int tx = threadIdx.x % TILE, ty = threadIdx.x / TILE;
+#pragma unroll
+  for (int q = 0; q < TILE / STEP; ++q) {
+    const int j = ty + STEP * q, kx = bx + j, ky = ky0 + by + tx;
+    if (kx < nx && by + tx < rows) {
+      const bool own = kx <= nx / 2;
+      const double v = own ? acc[(size_t)kx * ny + ky]
+                           : acc[(size_t)(nx - kx) * ny + (ky == 0 ? 0 : ny - ky)];
+      tile[j][tx] = own || !negate ? v : -v;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < TILE / STEP; ++q) {
+    const int j = ty + STEP * q, kx = bx + tx;
+    if (kx < nx && by + j < rows) out[(size_t)(by + j) * nx + kx] = tile[tx][j] * norm;
+  }
+}
+
+hipError_t launch_sk_expand(const double* acc, double* out, int nx, int ny, int ky0, int rows,
+                            double norm, int negate, hipStream_t st) {
+  hipLaunchKernelGGL(sk_expand_kernel, dim3((nx + 31) / 32, (rows + 31) / 32), dim3(256), 0, st,
+                     acc, out, nx, ny, ky0, rows, norm, negate);
+  return hipGetLastError();
+}
+
 static dim3 row_grid(int nx, int rows) { return dim3((nx + 255) / 256, rows); }
 
 // The row-parallel utility kernels below process the band of rows

@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -40,6 +41,120 @@ int hip_fail(hipError_t e, const char* what) {
     hipError_t e_ = (expr);                          \
     if (e_ != hipSuccess) return hip_fail(e_, #expr); \
   } while (0)
+
+// ---------------------------------------------------------------- readouts
+namespace {
+// Two areas: a small one for correlators, flags and the fields of small
+// lattices, and two halves for larger readouts.  Page-locked memory is slow to
+// allocate (the large area costs what it saves on one readout of 14 MB), so
+// the large one is allocated by the second readout that wants it.
+constexpr size_t kSmallBytes = (size_t)256 << 10, kStageBytes = (size_t)8 << 20;
+std::mutex g_stage_count_mu, g_stage_mu;  // the count; the areas
+int g_stage_users = 0;
+bool g_stage_wanted = false;
+char *g_small = nullptr, *g_stage = nullptr;
+
+char* locked_area(char*& area, size_t bytes) {
+  if (!area && hipHostMalloc((void**)&area, bytes, hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    area = nullptr;
+  }
+  return area;
+}
+}  // namespace
+
+Staging::Staging() {
+  std::lock_guard<std::mutex> lk(g_stage_count_mu);
+  ++g_stage_users;
+}
+
+Staging::~Staging() {
+  std::lock_guard<std::mutex> lk(g_stage_count_mu);
+  if (--g_stage_users > 0) return;
+  std::lock_guard<std::mutex> lk2(g_stage_mu);
+  for (char** a : {&g_small, &g_stage}) {
+    if (*a) (void)hipHostFree(*a);
+    *a = nullptr;
+  }
+  g_stage_wanted = false;
+}
+
+hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st) {
+  std::unique_lock<std::mutex> lk(g_stage_mu, std::try_to_lock);
+  size_t total = 0;
+  for (int i = 0; i < n; ++i) total += (pieces[i].bytes + 15) & ~(size_t)15;
+  char* area = nullptr;
+  if (lk.owns_lock()) {
+    if (total <= kSmallBytes) {
+      area = locked_area(g_small, kSmallBytes);
+    } else {
+      if (g_stage_wanted) area = locked_area(g_stage, 2 * kStageBytes);
+      g_stage_wanted = true;
+    }
+  }
+  if (!area) {
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = hipMemcpyAsync(pieces[i].dst, pieces[i].src, pieces[i].bytes,
+                                          hipMemcpyDeviceToHost, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipStreamSynchronize(st);
+  }
+  if (total <= kSmallBytes) {  // all at once, one wait
+    size_t o = 0;
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e =
+          hipMemcpyAsync(area + o, pieces[i].src, pieces[i].bytes, hipMemcpyDeviceToHost, st);
+      if (e != hipSuccess) {
+        (void)hipStreamSynchronize(st);
+        return e;
+      }
+      o += (pieces[i].bytes + 15) & ~(size_t)15;
+    }
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    o = 0;
+    for (int i = 0; i < n; ++i) {
+      std::memcpy(pieces[i].dst, area + o, pieces[i].bytes);
+      o += (pieces[i].bytes + 15) & ~(size_t)15;
+    }
+    return hipSuccess;
+  }
+  // in halves: one is copied on to the caller while the other fills
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  hipError_t e = hipEventCreateWithFlags(&ev[0], hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[1], hipEventDisableTiming);
+  char* dst[2] = {nullptr, nullptr};
+  size_t len[2] = {0, 0};
+  int h = 0;
+  auto drain = [&](int k) {
+    if (!dst[k]) return hipSuccess;
+    // a half takes some 40 us: asked for, not slept on
+    hipError_t r = hipErrorNotReady;
+    while (r == hipErrorNotReady) r = hipEventQuery(ev[k]);
+    if (r == hipSuccess) std::memcpy(dst[k], area + (size_t)k * kStageBytes, len[k]);
+    dst[k] = nullptr;
+    return r;
+  };
+  for (int i = 0; i < n && e == hipSuccess; ++i)
+    for (size_t o = 0; o < pieces[i].bytes && e == hipSuccess; o += kStageBytes, h ^= 1) {
+      e = drain(h);
+      if (e != hipSuccess) break;
+      len[h] = std::min(kStageBytes, pieces[i].bytes - o);
+      e = hipMemcpyAsync(area + (size_t)h * kStageBytes, (const char*)pieces[i].src + o, len[h],
+                         hipMemcpyDeviceToHost, st);
+      if (e == hipSuccess) e = hipEventRecord(ev[h], st);
+      if (e == hipSuccess) dst[h] = (char*)pieces[i].dst + o;
+    }
+  for (int k = 0; k < 2; ++k, h ^= 1) {
+    const hipError_t r = e == hipSuccess ? drain(h) : hipSuccess;
+    if (e == hipSuccess) e = r;
+  }
+  if (e != hipSuccess) (void)hipStreamSynchronize(st);  // nothing in flight into the area
+  for (hipEvent_t v : ev)
+    if (v) (void)hipEventDestroy(v);
+  return e;
+}
 
 // ------------------------------------------------------------ host math
 // Hermite rows of eq. (A3) and the D2Q9 weights of eq. (A2).
@@ -295,20 +410,22 @@ static void cov_from(const double* S, double n, double C[81]) {
     }
 }
 
+// B C B^T, each element its sum in index order; the element's column runs in
+// the innermost loops, which vectorise (every closed record takes two of these).
 static void transform(const double B[81], const double C[81], double out[81]) {
-  double T[81];
+  double T[81], BT[81];
   for (int a = 0; a < 9; ++a)
-    for (int j = 0; j < 9; ++j) {
-      double s = 0;
-      for (int i = 0; i < 9; ++i) s += B[a * 9 + i] * C[i * 9 + j];
-      T[a * 9 + j] = s;
+    for (int j = 0; j < 9; ++j) BT[j * 9 + a] = B[a * 9 + j];
+  auto product = [](const double X[81], const double Y[81], double Z[81]) {
+    for (int a = 0; a < 9; ++a) {
+      double z[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+      for (int i = 0; i < 9; ++i)
+        for (int j = 0; j < 9; ++j) z[j] += X[a * 9 + i] * Y[i * 9 + j];
+      for (int j = 0; j < 9; ++j) Z[a * 9 + j] = z[j];
     }
-  for (int a = 0; a < 9; ++a)
-    for (int b = 0; b < 9; ++b) {
-      double s = 0;
-      for (int j = 0; j < 9; ++j) s += T[a * 9 + j] * B[b * 9 + j];
-      out[a * 9 + b] = s;
-    }
+  };
+  product(B, C, T);
+  product(T, BT, out);
 }
 
 // Final correlators from the closed block records (nb x 54, host copy) and

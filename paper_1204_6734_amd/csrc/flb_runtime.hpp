@@ -32,6 +32,31 @@ void hermite_rows(double m[81]);
 double equilibrium(int i, double rho, double ux, double uy);
 bool fnorm_rows(double ux, double uy, double mt[81]);
 
+// Readouts to caller-owned host memory go through page-locked staging: a copy
+// of 14 MB straight into pageable memory takes 0.86 ms, through it 0.45, and
+// every small piece 10 to 15 us.  The staging is the process's, held while any
+// lattice or server exists (Staging members count them); a thread that finds
+// it in use copies straight.
+class Staging {
+ public:
+  Staging();
+  ~Staging();
+  Staging(const Staging&) = delete;
+  Staging& operator=(const Staging&) = delete;
+};
+// One piece of a readout: bytes from device memory to the host.
+struct HostPiece {
+  void* dst;
+  const void* src;
+  size_t bytes;
+};
+// Copies the pieces behind the work already enqueued on st and waits for them.
+hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st);
+inline hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t st) {
+  const HostPiece p{dst, src, bytes};
+  return copy_out(&p, 1, st);
+}
+
 struct Stats {
   uint64_t tb_len = 0, tb_fill = 0, nb = 0, nsamples = 0;
   int max_blocks = kMaxTimeBlocks;  // record capacity (even)
@@ -89,6 +114,11 @@ hipError_t launch_fill(double* p, size_t n, double v, hipStream_t st);
 hipError_t launch_stream_copy(const void* in, void* out, size_t n4, hipStream_t st);
 hipError_t launch_stream_probe(int storage, void* pop, int nx, int ny, uint32_t pitch, int wide,
                                int tiles_x, int ntiles, int odd, hipStream_t st);
+// out[ky - ky0][kx] = norm acc[kx][ky] for rows ky0 .. ky0 + rows of the full
+// plane, the half kx > nx/2 from its partner at -k (negated there for the
+// imaginary part of the cross term)
+hipError_t launch_sk_expand(const double* acc, double* out, int nx, int ny, int ky0, int rows,
+                            double norm, int negate, hipStream_t st);
 hipError_t sk_prepare(size_t max_lds);
 hipError_t launch_sk_sample(int storage, void* z, void* zt, double* acc, int nx, int ny,
                             const void* twx, const void* twy, size_t max_lds, hipStream_t st);

@@ -114,10 +114,11 @@ static size_t request_bytes_of(const flb_params& p, int storage) {
 using namespace flb;
 
 struct flb_server {
+  Staging staging;
   flb_server_config cfg;
   hipStream_t st = nullptr;
   bool own_stream = false;
-  char* arena = nullptr;
+  char *arena = nullptr, *tables = nullptr;
   FreeList fl;
   std::mutex mu;
   std::condition_variable cv, done_cv;
@@ -228,18 +229,20 @@ int flb_server::finish(const Active& a) {
   res.t_submit = a.t_submit;
   res.t_admit = a.t_admit;
   int err = 0;
-  HIPC(hipMemcpy(&err, a.desc.err, 4, hipMemcpyDeviceToHost));
+  double open[kNStat];
+  std::vector<double> recs((size_t)std::max<uint64_t>(a.stats.nb, 1) * kNStat);
+  HostPiece piece[3] = {{&err, a.desc.err, 4}};
+  int n = 1;
+  if (a.desc.partials) {
+    HIPC(launch_open_sum(a.desc.partials, a.desc.ntiles, d_open, d_open + kNStat, st));
+    piece[n++] = {open, d_open, sizeof(open)};
+    if (a.stats.nb)
+      piece[n++] = {recs.data(), records_of(a, arena, cfg.precision), a.stats.nb * kNStat * 8};
+  }
+  HIPC(copy_out(piece, n, st));
   res.status = err ? ((err & kErrInvalidVelocity) ? FLB_E_INVALID_VELOCITY : FLB_E_NONFINITE)
                    : FLB_OK;
   if (a.desc.partials && !err) {
-    double* rec = records_of(a, arena, cfg.precision);
-    HIPC(launch_open_sum(a.desc.partials, a.desc.ntiles, d_open, d_open + kNStat, st));
-    double open[kNStat];
-    std::vector<double> recs((size_t)std::max<uint64_t>(a.stats.nb, 1) * kNStat);
-    HIPC(hipMemcpyAsync(open, d_open, sizeof(open), hipMemcpyDeviceToHost, st));
-    if (a.stats.nb)
-      HIPC(hipMemcpyAsync(recs.data(), rec, a.stats.nb * kNStat * 8, hipMemcpyDeviceToHost, st));
-    HIPC(hipStreamSynchronize(st));
     double mt0[81];
     fnorm_rows(a.p.ux0, a.p.uy0, mt0);
     finish_covariance(a.stats, recs, open, (uint64_t)a.p.nx * a.p.ny, mt0, &res.cov);
@@ -386,14 +389,19 @@ int flb_server_create(const flb_server_config* cfg, void* hip_stream, flb_server
   if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "server arena of %zu bytes",
                                              cfg->mem_budget_bytes));
   S->fl.reset(cfg->mem_budget_bytes);
-  for (int c = 0; c < 2; ++c) {
-    e = hipMalloc((void**)&S->d_slots[c], (size_t)cfg->max_slots * sizeof(SlotDesc));
-    if (e == hipSuccess) e = hipMalloc((void**)&S->d_prefix[c], (cfg->max_slots + 1) * sizeof(int));
-    if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "slot tables"));
+  // the slot tables, the clock and the open sums in one allocation
+  for (int pass = 0; pass < 2; ++pass) {
+    Arena a;
+    a.base = S->tables;
+    for (int c = 0; c < 2; ++c) {
+      S->d_slots[c] = a.take<SlotDesc>(cfg->max_slots);
+      S->d_prefix[c] = a.take<int>((size_t)cfg->max_slots + 1);
+    }
+    S->d_clock = a.take<uint64_t>(1);
+    S->d_open = a.take<double>((size_t)(1 + kFoldRows) * kNStat);
+    if (pass == 0 && hipMalloc((void**)&S->tables, a.used) != hipSuccess)
+      return fail(set_error(FLB_E_OOM, "slot tables"));
   }
-  e = hipMalloc((void**)&S->d_clock, 8);
-  if (e == hipSuccess) e = hipMalloc((void**)&S->d_open, (size_t)(1 + kFoldRows) * kNStat * sizeof(double));
-  if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "clock"));
   e = hipMemsetAsync(S->d_clock, 0, 8, S->st);
   if (e == hipSuccess) e = hipStreamSynchronize(S->st);
   if (e != hipSuccess) return fail(hip_fail(e, "clock init"));
@@ -517,12 +525,7 @@ void flb_server_destroy(flb_server* S) {
   S->cv.notify_all();
   if (S->worker.joinable()) S->worker.join();
   if (S->st) (void)hipStreamSynchronize(S->st);
-  for (int c = 0; c < 2; ++c) {
-    if (S->d_slots[c]) (void)hipFree(S->d_slots[c]);
-    if (S->d_prefix[c]) (void)hipFree(S->d_prefix[c]);
-  }
-  if (S->d_clock) (void)hipFree(S->d_clock);
-  if (S->d_open) (void)hipFree(S->d_open);
+  if (S->tables) (void)hipFree(S->tables);
   if (S->arena) (void)hipFree(S->arena);
   if (S->own_stream && S->st) (void)hipStreamDestroy(S->st);
   delete S;

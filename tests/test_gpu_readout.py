@@ -1,0 +1,67 @@
+"""Readouts through page-locked staging: pieces around the sizes where the
+staging changes (small area, straight, two halves filled in turn), several
+readouts in a row, and from several threads at once."""
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+# 9 nx ny doubles: below, at and above 256 KiB; above 8 and 16 MiB; 37 MB
+@pytest.mark.parametrize("nx,ny", [(10, 7), (64, 56), (64, 57), (64, 58), (400, 300), (500, 480),
+                                   (1000, 520)])
+def test_whole_readout_equals_row_readouts(flb, nx, ny):
+    L = flb.Lattice(flb.make_params(nx, ny, precision=flb.FP64, ux0=0.1, kT=1e-4, seed=nx,
+                                    init=flb.INIT_THERMAL, sample_every=1))
+    L.step(3)
+    rows = np.concatenate([L.rows(y, min(37, ny - y)) for y in range(0, ny, 37)], axis=1)
+    for _ in range(3):
+        np.testing.assert_array_equal(L.populations(), rows)
+        blob = L.checkpoint()
+    L.step(2)
+    L.restore(blob)
+    np.testing.assert_array_equal(L.populations(), rows)
+    L.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(21, 21), (32, 9), (9, 64), (64, 33)])
+def test_structure_factors_are_symmetric(flb, nx, ny):
+    L = flb.Lattice(flb.make_params(nx, ny, precision=flb.FP64, ux0=0.1, kT=1e-4, seed=5,
+                                    init=flb.INIT_THERMAL, sk_every=1))
+    L.step(4)
+    for w in range(5):
+        s = L.structure_factor(w)
+        m = np.roll(s[::-1, ::-1], (1, 1), (0, 1))  # the value at -k
+        own = np.ones((ny, nx), bool)
+        own[:, 0] = False
+        if nx % 2 == 0:
+            own[:, nx // 2] = False
+        np.testing.assert_array_equal(s[own], -m[own] if w == flb.SK_JXJY_IM else m[own])
+    L.close()
+
+
+def test_readouts_from_several_threads(flb):
+    """Threads reading their own lattices share the staging or copy straight."""
+    lats = [flb.Lattice(flb.make_params(300 + 40 * k, 200, kT=1e-4, seed=k, ux0=0.02 * k,
+                                        init=flb.INIT_THERMAL, sample_every=1))
+            for k in range(4)]
+    want = []
+    for L in lats:
+        L.step(5)
+        want.append((L.populations(), L.covariance()["cov_f"]))
+    bad = []
+
+    def work(k):
+        for _ in range(10):
+            f, c = lats[k].populations(), lats[k].covariance()["cov_f"]
+            if not (np.array_equal(f, want[k][0]) and np.array_equal(c, want[k][1])):
+                bad.append(k)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
