@@ -263,6 +263,10 @@ Group::~Group() {
   }
   if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
   if (graph) (void)hipGraphDestroy(graph);
+  for (int i = 0; i < kMaxBranches; ++i) {
+    if (joined[i]) (void)hipEventDestroy(joined[i]);
+    if (branch[i]) (void)hipStreamDestroy(branch[i]);
+  }
   if (own_mem && dev) (void)hipFree(dev);
   if (own_stream && st) (void)hipStreamDestroy(st);
 }
@@ -319,15 +323,24 @@ int Group::after_step(uint64_t tt, bool replayed) {
   return FLB_OK;
 }
 
-// The step launches of one step: one per compute class.
-hipError_t Group::launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c) {
+// The step launches of one step: one per compute class, of all members or of
+// one of `parts` equal shares of them (members of one tile count: the prefix
+// sums of a share are the first ones) on stream q.
+hipError_t Group::launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c, int part,
+                                 int parts, hipStream_t q) {
   for (int i = 0; i < nclass; ++i) {
-    const hipError_t e = launch_step(storage, ccompute[i], basis, sample, odd, d_slots + cfirst[i],
-                                     d_prefix + cfirst[i] + i, ccount[i], ctiles[i], d_clock, k,
-                                     c, st);
+    const int a = ccount[i] * part / parts, b = ccount[i] * (part + 1) / parts;
+    if (a == b) continue;
+    const hipError_t e =
+        launch_step(storage, ccompute[i], basis, sample, odd, d_slots + cfirst[i] + a,
+                    d_prefix + cfirst[i] + i, b - a,
+                    parts == 1 ? ctiles[i] : (b - a) * hdesc[0].ntiles, d_clock, k, c, q);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+hipError_t Group::launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c) {
+  return launch_classes(k, sample, odd, c, 0, 1, st);
 }
 
 // fn() enqueues `steps` steps; with profiling on, between two events.
@@ -465,6 +478,22 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
   return hipSuccess;
 }
 
+// Branches of a captured chunk.  Members do not depend on each other, so two
+// halves can advance side by side: while one half's step ends and its next one
+// starts, the other's fills the chip.  A branch costs the replay 7.8 us a step
+// at least, so the chunk stays one chain below the tiles whose step takes
+// about that (FP32 2048 tiles of 256 sites, FP64 1024).  Measured (us a step,
+// one branch -> two; more gained nothing): FP32 1024 tiles 5.7 -> 7.8, 2048 9.2
+// -> 8.1, 4096 (64 x 128^2) 16.2 -> 13.5, 16384 51.6 -> 46.9, 32768 101.5 ->
+// 100.1; FP64 512 tiles 5.3 -> 7.9, 1024 9.7 -> 8.4, 2048 17.8 -> 13.8, 16384
+// 116.5 -> 112.6.
+int Group::graph_branches() const {
+  if (P.size() < 2 || multi_max || d_skacc) return 1;
+  for (auto& h : hdesc)
+    if (h.ntiles != hdesc[0].ntiles) return 1;
+  return two_branches(compute, total_tiles) ? 2 : 1;
+}
+
 int Group::abandon_capture(hipError_t e) {
   hipGraph_t g = nullptr;
   (void)hipStreamEndCapture(st, &g);
@@ -474,7 +503,19 @@ int Group::abandon_capture(hipError_t e) {
 
 int Group::capture_graph() {
   if (graph_exec) return FLB_OK;
+  const int parts = graph_branches();
+  for (int i = 1; i < parts; ++i) {
+    if (!branch[i]) HIPC(hipStreamCreateWithFlags(&branch[i], hipStreamNonBlocking));
+    if (!joined[i]) HIPC(hipEventCreateWithFlags(&joined[i], hipEventDisableTiming));
+  }
+  if (!joined[0]) HIPC(hipEventCreateWithFlags(&joined[0], hipEventDisableTiming));
   HIPC(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+  if (parts > 1) {
+    hipError_t e = hipEventRecord(joined[0], st);
+    for (int i = 1; i < parts && e == hipSuccess; ++i)
+      e = hipStreamWaitEvent(branch[i], joined[0], 0);
+    if (e != hipSuccess) return abandon_capture(e);
+  }
   for (int k = 0; k < graph_chunk; ++k) {
     int pass[2];
     pass_pair((uint64_t)k, (uint64_t)(graph_chunk - k), false, &pass[0], &pass[1]);
@@ -498,11 +539,18 @@ int Group::capture_graph() {
     bool sample = false;
     for (int s = 0; s < (int)P.size(); ++s)
       sample |= sample_due(s, (uint64_t)k) || sk_due(s, (uint64_t)k);
-    hipError_t e = launch_classes((uint32_t)k, sample, k & 1, launch);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < parts && e == hipSuccess; ++i)
+      e = launch_classes((uint32_t)k, sample, k & 1, launch, i, parts, i ? branch[i] : st);
     for (int s = 0; s < (int)P.size() && e == hipSuccess; ++s)
       if (sk_due(s, (uint64_t)k))
         e = launch_sk_sample(storage, d_z, d_zt, d_skacc, P[s].nx, P[s].ny, d_twx, d_twy,
                              max_lds, st);
+    if (e != hipSuccess) return abandon_capture(e);
+  }
+  for (int i = 1; i < parts; ++i) {
+    hipError_t e = hipEventRecord(joined[i], branch[i]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, joined[i], 0);
     if (e != hipSuccess) return abandon_capture(e);
   }
   HIPC(launch_tick(d_clock, (uint64_t)graph_chunk, st));

@@ -76,6 +76,11 @@ struct Group {
   int graph_chunk = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
+  // side branches of the captured graph: their streams (from 1) and the
+  // events that fork (0) and join them
+  static constexpr int kMaxBranches = 2;
+  hipStream_t branch[kMaxBranches] = {nullptr};
+  hipEvent_t joined[kMaxBranches] = {nullptr};
   // profiling
   bool profiling = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
@@ -96,6 +101,9 @@ struct Group {
   template <typename Fn>
   int profiled(Fn fn, uint64_t steps);
   hipError_t launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c);
+  hipError_t launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c, int part, int parts,
+                            hipStream_t q);
+  int graph_branches() const;
   bool graph_friendly() const;
   uint64_t steps_to_close(uint64_t tt, uint64_t skip) const;
   int abandon_capture(hipError_t e);

@@ -22,6 +22,9 @@ int set_error(int code, const char* fmt, ...);
 int hip_fail(hipError_t e, const char* what);
 int check_params(const flb_params* p);
 int compute_precision(const flb_params* p);
+// Whether this many tiles of independent lattices are stepped faster as two
+// halves side by side (compute: 0 FP64, 1 FP32).
+inline bool two_branches(int compute, int tiles) { return tiles >= (compute == 0 ? 1024 : 2048); }
 uint32_t row_pitch(int nx);
 size_t population_elems(int nx, int ny);
 void tile_shape(const flb_params& p, int* wide, int* tiles_x, int* ntiles);

@@ -134,8 +134,10 @@ struct flb_server {
   double* d_open = nullptr;
   std::vector<SlotDesc> h_slots[2];
   std::vector<int> h_prefix[2];
-  std::vector<int> members[2];  // indices into `active`
-  int tiles[2] = {0, 0};
+  // the second of the two streams a chunk may run on, and the events that
+  // fork and join it
+  hipStream_t st2 = nullptr;
+  hipEvent_t forked = nullptr, joined = nullptr;
   std::chrono::steady_clock::time_point t_start;
   double busy = 0;
   std::thread worker;
@@ -278,50 +280,89 @@ int flb_server::retire() {
 }
 
 // One chunk: upload the slot tables, launch chunk_steps batched steps, tick.
+// Requests do not depend on each other, so the requests of a class are dealt
+// to two halves of about the same number of tiles that advance on two streams,
+// one filling the chip while the other's step ends, where the steps are long
+// enough for twice the launches (two_branches).
 int flb_server::run_chunk() {
   const int K = cfg.chunk_steps;
+  struct Half {
+    int cls, first, count, tiles, prefix_at;
+    hipStream_t q;
+  };
+  std::vector<Half> halves;
+  std::vector<hipStream_t> stream_of(active.size(), st);
+  bool two = false;
   for (int c = 0; c < 2; ++c) {
-    members[c].clear();
     h_slots[c].clear();
-    h_prefix[c].assign(1, 0);
-  }
-  for (int i = 0; i < (int)active.size(); ++i) {
-    const int c = active[i].cls;
-    members[c].push_back(i);
-    h_slots[c].push_back(active[i].desc);
-    h_prefix[c].push_back(h_prefix[c].back() + active[i].desc.ntiles);
-  }
-  for (int c = 0; c < 2; ++c) {
-    tiles[c] = h_prefix[c].back();
-    if (members[c].empty()) continue;
+    h_prefix[c].clear();
+    int total = 0, n = 0;
+    for (auto& a : active)
+      if (a.cls == c) {
+        total += a.desc.ntiles;
+        ++n;
+      }
+    if (!n) continue;
+    const bool split = n > 1 && two_branches(c, total);
+    // in order, each request to the lighter half
+    int load[2] = {0, 0};
+    std::vector<int> half(active.size(), 0);
+    if (split)
+      for (size_t i = 0; i < active.size(); ++i)
+        if (active[i].cls == c) {
+          half[i] = load[1] < load[0];
+          load[half[i]] += active[i].desc.ntiles;
+        }
+    for (int p = 0; p < (split ? 2 : 1); ++p) {
+      Half h{c, (int)h_slots[c].size(), 0, 0, (int)h_prefix[c].size(), p ? st2 : st};
+      h_prefix[c].push_back(0);
+      for (size_t i = 0; i < active.size(); ++i) {
+        if (active[i].cls != c || half[i] != p) continue;
+        h_slots[c].push_back(active[i].desc);
+        h.tiles += active[i].desc.ntiles;
+        h_prefix[c].push_back(h.tiles);
+        ++h.count;
+        stream_of[i] = h.q;
+      }
+      if (h.count) halves.push_back(h);
+      two = two || (p == 1 && h.count);
+    }
     HIPC(hipMemcpyAsync(d_slots[c], h_slots[c].data(), h_slots[c].size() * sizeof(SlotDesc),
                         hipMemcpyHostToDevice, st));
     HIPC(hipMemcpyAsync(d_prefix[c], h_prefix[c].data(), h_prefix[c].size() * sizeof(int),
                         hipMemcpyHostToDevice, st));
   }
+  if (two) {
+    HIPC(hipEventRecord(forked, st));
+    HIPC(hipStreamWaitEvent(st2, forked, 0));
+  }
   const int storage = cfg.precision == 0 ? 0 : 1;
   for (int k = 0; k < K; ++k) {
-    // the sampling variant only where some request of the class samples
-    bool due[2] = {false, false};
-    for (auto& a : active) {
-      const uint64_t own = a.desc.t0 + clock + (uint64_t)k;
-      due[a.cls] |= own < a.nsteps && a.p.sample_every > 0 && own % (uint64_t)a.p.sample_every == 0;
-    }
-    for (int c = 0; c < 2; ++c) {
-      if (members[c].empty()) continue;
-      const bool any_sample = due[c];
+    for (const Half& h : halves) {
+      // the sampling variant only where some request of the half samples
+      bool due = false;
+      for (int i = h.first; i < h.first + h.count; ++i) {
+        const SlotDesc& d = h_slots[h.cls][i];
+        const uint64_t own = d.t0 + clock + (uint64_t)k;
+        due |= own < d.tend && d.sample_every > 0 && own % (uint64_t)d.sample_every == 0;
+      }
       // chunk_steps is even, so every request's own time has the parity of k
-      HIPC(launch_step(storage, c, cfg.basis, any_sample, k & 1, d_slots[c], d_prefix[c],
-                       (int)members[c].size(), tiles[c], d_clock, (uint32_t)k, LaunchCfg{},
-                       st));
+      HIPC(launch_step(storage, h.cls, cfg.basis, due, k & 1, d_slots[h.cls] + h.first,
+                       d_prefix[h.cls] + h.prefix_at, h.count, h.tiles, d_clock, (uint32_t)k,
+                       LaunchCfg{}, h.q));
     }
-    for (auto& a : active) {
+    for (size_t i = 0; i < active.size(); ++i) {
+      Active& a = active[i];
       const uint64_t own = a.desc.t0 + clock + (uint64_t)k;
       if (own >= a.nsteps || a.p.sample_every <= 0) continue;
       if (own % (uint64_t)a.p.sample_every != 0) continue;
       HIPC(a.stats.after_sample((uint64_t)a.p.nx * a.p.ny, a.desc.partials, a.desc.ntiles,
-                                records_of(a, arena, cfg.precision), st));
+                                records_of(a, arena, cfg.precision), stream_of[i]));
     }
+  }
+  if (two) {
+    HIPC(hipEventRecord(joined, st2));
+    HIPC(hipStreamWaitEvent(st, joined, 0));
   }
   HIPC(launch_tick(d_clock, (uint64_t)K, st));
   clock += (uint64_t)K;
@@ -385,6 +426,10 @@ int flb_server_create(const flb_server_config* cfg, void* hip_stream, flb_server
     if (e != hipSuccess) return fail(hip_fail(e, "stream"));
     S->own_stream = true;
   }
+  e = hipStreamCreateWithFlags(&S->st2, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&S->forked, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&S->joined, hipEventDisableTiming);
+  if (e != hipSuccess) return fail(hip_fail(e, "second stream"));
   e = hipMalloc((void**)&S->arena, cfg->mem_budget_bytes);
   if (e != hipSuccess) return fail(set_error(FLB_E_OOM, "server arena of %zu bytes",
                                              cfg->mem_budget_bytes));
@@ -395,7 +440,7 @@ int flb_server_create(const flb_server_config* cfg, void* hip_stream, flb_server
     a.base = S->tables;
     for (int c = 0; c < 2; ++c) {
       S->d_slots[c] = a.take<SlotDesc>(cfg->max_slots);
-      S->d_prefix[c] = a.take<int>((size_t)cfg->max_slots + 1);
+      S->d_prefix[c] = a.take<int>((size_t)cfg->max_slots + 2);  // of two halves
     }
     S->d_clock = a.take<uint64_t>(1);
     S->d_open = a.take<double>((size_t)(1 + kFoldRows) * kNStat);
@@ -524,9 +569,13 @@ void flb_server_destroy(flb_server* S) {
   }
   S->cv.notify_all();
   if (S->worker.joinable()) S->worker.join();
+  if (S->st2) (void)hipStreamSynchronize(S->st2);
   if (S->st) (void)hipStreamSynchronize(S->st);
   if (S->tables) (void)hipFree(S->tables);
   if (S->arena) (void)hipFree(S->arena);
+  if (S->forked) (void)hipEventDestroy(S->forked);
+  if (S->joined) (void)hipEventDestroy(S->joined);
+  if (S->st2) (void)hipStreamDestroy(S->st2);
   if (S->own_stream && S->st) (void)hipStreamDestroy(S->st);
   delete S;
 }

@@ -91,6 +91,24 @@ def test_ensembles(flb, prec):
                 np.testing.assert_array_equal(v, co[k], err_msg=k)
 
 
+def test_replicas_in_two_graph_branches_equal_alone(flb):
+    """Enough tiles that a captured chunk advances two halves side by side
+    (and, with an odd count, unequal ones), in both compute classes."""
+    ps = [flb.make_params(128, 120, ux0=0.3 if k % 7 == 3 else 0.01 * k, kT=1e-4, seed=k,
+                          sample_every=3, block_steps=5) for k in range(35)]
+    E = flb.Ensemble(ps, graph_chunk=12)
+    for n in (24, 7, 29):  # replays between eager steps
+        E.step(n)
+        E.sync()
+    for i in (0, 3, 16, 17, 18, 34):
+        L = flb.Lattice(ps[i])
+        L.step(60)
+        np.testing.assert_array_equal(E.populations(i), L.populations())
+        ce, cl = E.covariance(i), L.covariance()
+        for k, v in ce.items():
+            np.testing.assert_array_equal(v, cl[k], err_msg=k)
+
+
 def test_an_error_has_the_same_step(flb):
     kw = dict(precision=flb.FP32_SHIFTED, kT=0.05, seed=7, init=flb.INIT_THERMAL)
     a, b = pair(flb, 40, 40, **kw)
