@@ -42,6 +42,38 @@ def test_structure_factors_are_symmetric(flb, nx, ny):
     L.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(8, 8), (8, 2048), (16, 64), (512, 8), (512, 1024), (128, 30),
+                                   (1024, 16), (64, 4)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_structure_factors_equal_numpy(flb, nx, ny, prec):
+    """One sample of a known state at the edges of the transforms' ranges:
+    the two-kernel one takes powers of two up to 512 x 2048."""
+    fp64 = prec == "fp64"
+    L = flb.Lattice(flb.make_params(nx, ny, precision=flb.FP64 if fp64 else flb.FP32_SHIFTED,
+                                    ux0=0.1, uy0=-0.02, kT=1e-4, seed=9, init=flb.INIT_THERMAL,
+                                    sk_every=1))
+    L.step(2)
+    f = L.populations()
+    L.reset_stats()
+    L.step(1)
+    vx = np.array([0, 1, 0, -1, 0, 1, -1, -1, 1.0])
+    vy = np.array([0, 0, 1, 0, -1, 1, 1, -1, -1.0])
+    r = f.sum(0) - 1.0
+    jx = np.tensordot(vx, f, 1) - 0.1
+    jy = np.tensordot(vy, f, 1) + 0.02
+    a, b, c = (np.fft.fft2(x) for x in (r, 3 ** .5 * (jx - 0.1 * r), 3 ** .5 * (jy + 0.02 * r)))
+    x = b * c.conj()
+    want = [abs(a) ** 2, abs(b) ** 2, abs(c) ** 2, x.real, x.imag]
+    # FP32: fields and transform carry 2^-24 each, ~log2(n) roundings of the
+    # transform; squares double it.  FP64 the same with 2^-53 (and the fields'
+    # difference from 1: 2^-53 of 1 against fluctuations of 1e-2).
+    tol = 1e-11 if fp64 else 5e-6
+    for w in range(5):
+        got = L.structure_factor(w) * (nx * ny)
+        assert np.abs(got - want[w]).max() <= tol * max(np.abs(want[k]).max() for k in (0, 1, 2))
+    L.close()
+
+
 def test_readouts_from_several_threads(flb):
     """Threads reading their own lattices share the staging or copy straight."""
     lats = [flb.Lattice(flb.make_params(300 + 40 * k, 200, kT=1e-4, seed=k, ux0=0.02 * k,
