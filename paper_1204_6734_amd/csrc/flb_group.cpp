@@ -142,7 +142,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
       if (second) need_bytes = both.used + 256;
     }
     if (!second) {
-      multi_max = 0;
+      multi_max = march_rows = 0;
       e = hipMalloc(&dev, need_bytes);
     }
     if (e != hipSuccess) {
@@ -168,7 +168,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
                      "%d (FP32) or at most %d",
                      (int)(max_lds / sizeof(double2)), (int)(max_lds / sizeof(float2)),
                      kMaxDirectDft);
-  if (multi_max)
+  if (multi_max && !march_rows)
     for (int c = 0; c < nclass; ++c) 
       HIPC(multi_prepare(storage, ccompute[c], basis, P[0].nx, multi_max, max_lds));
   launch = tuned_launch(*this);
@@ -408,6 +408,12 @@ uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
 void Group::plan_multi(int cus) {
   multi_max = 0;
   std::fill(&multi_nt[0][0], &multi_nt[0][0] + 2 * (kMultiMaxSteps + 1), 0);
+  march_rows = plan_march(cus);
+  if (march_rows) {
+    multi_nt[0][2] = 1;  // steps without sums only
+    multi_max = 2;
+    return;
+  }
   const int nx = P[0].nx;
   const bool narrow = nx <= kTileX / 2;
   if (hdesc[0].wide || (compute == 0 && !narrow)) return;
@@ -421,13 +427,40 @@ void Group::plan_multi(int cus) {
       }
 }
 
-// Whether a second population buffer of this size is taken: small ones
-// always, larger ones when they leave the caller most of the free memory.
+// Rows a wavefront of step_march_kernel takes, 0 where one step per launch is
+// the better one.  Two steps per pass over memory halve the traffic and cost
+// (64/62)(1 + 1/H) of the arithmetic, so they pay where the populations do not
+// stay in the 256 MiB last-level cache and the arithmetic is the FP32 one (FP64
+// is bound by it).  us a step, one step per launch -> this kernel: 2560^2 (225
+// MiB) 71 -> 78, 2003x4001 (275) 95.5 -> 96.4, 512x16384 (288) 100 -> 101,
+// 2900^2 (289) 105 -> 100, 3072^2 (324) 116 -> 107, 4096^2 214 -> 189, 8192^2
+// 845 -> 717.  Narrow members waste lanes of their last strip: 200^2 x 256 (78 %
+// used) 160 -> 138, 256^2 x 256 (80 %) 223 -> 211, 128^2 x 1000 (67 %) 217 ->
+// 239.  32 rows once that is four rounds of the 16 wavefronts a compute unit
+// holds (8192^2 727 -> 717, 512^2 x 128 389 -> 384), 16 below (4096^2 191 ->
+// 189, 2816^2 92 -> 91).
+int Group::plan_march(int cus) const {
+  const int nx = P[0].nx, ny = P[0].ny, n = (int)P.size();
+  if (storage != 1 || compute != 1) return 0;
+  if ((double)nx * ny * n * 36.0 < (double)((size_t)300 << 20)) return 0;
+  const int strips = (nx + kMarchCols - 1) / kMarchCols;
+  if (4 * nx < 3 * 64 * strips) return 0;
+  const double waves = (double)strips * ((ny + 31) / 32) * n;
+  return waves >= 64.0 * cus ? 32 : 16;
+}
+
+// Whether a second population buffer of this size is taken: small ones always,
+// larger ones where seven eighths of the device's memory stay free beside both
+// buffers (so that programs which fill the memory find it as large as before;
+// 16384 x 16384 takes twice 9.7 of 288 GB).
 bool Group::take_second(size_t bytes) const {
   if (bytes <= ((size_t)256 << 20)) return true;
   size_t freeb = 0, total = 0;
-  if (hipMemGetInfo(&freeb, &total) != hipSuccess) return false;
-  return bytes <= freeb / 8;
+  if (hipMemGetInfo(&freeb, &total) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return (double)freeb - (double)need_bytes - (double)bytes >= 0.875 * (double)total;
 }
 
 // Largest launch from the even time tt within `lim` steps that holds no
@@ -468,6 +501,9 @@ void Group::pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb)
 
 // One launch of K steps from time tt (step index k of the device clock).
 hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
+  if (march_rows)
+    return launch_step_march(basis, d_slots, (int)P.size(), P[0].nx, P[0].ny, march_rows, flip,
+                             d_clock, k, st);
   const bool sample = pass_samples(tt, K);
   for (int i = 0; i < nclass; ++i) {
     const hipError_t e =

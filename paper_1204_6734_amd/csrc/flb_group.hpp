@@ -72,6 +72,9 @@ struct Group {
   char* pop2 = nullptr;
   int multi_nt[2][kMultiMaxSteps + 1] = {{0}};
   int multi_max = 0;
+  // rows a wavefront of the two-step pass over a large lattice takes (0: the
+  // launches of several steps are those of small lattices)
+  int march_rows = 0;
   // graphs
   int graph_chunk = 0;
   hipGraph_t graph = nullptr;
@@ -108,6 +111,7 @@ struct Group {
   uint64_t steps_to_close(uint64_t tt, uint64_t skip) const;
   int abandon_capture(hipError_t e);
   void plan_multi(int cus);
+  int plan_march(int cus) const;
   bool take_second(size_t bytes) const;
   int pass_steps(uint64_t tt, uint64_t lim) const;
   bool pass_samples(uint64_t tt, int K) const;

@@ -30,4 +30,13 @@ hipError_t launch_step_multi(int storage, int compute, int basis, bool sample,
                              int flip, const uint64_t* d_clock, uint32_t step_idx,
                              hipStream_t st);
 
+constexpr int kMarchCols = 62;  // columns a wavefront of step_march_kernel stores
+
+// Two steps of nslots large lattices (FP32 storage and collision, no sums or
+// fields due, the first step at an even time) in one pass over memory, H rows
+// a wavefront, pop -> pop2 (flip: pop2 -> pop).
+hipError_t launch_step_march(int basis, const SlotDesc* d_slots, int nslots, int nx, int ny,
+                             int H, int flip, const uint64_t* d_clock, uint32_t step_idx,
+                             hipStream_t st);
+
 }  // namespace flb

@@ -1,0 +1,80 @@
+"""Two steps per pass over memory (FP32 lattices larger than the last-level
+cache) against one step per launch, which a forced launch shape selects: the
+same bit for bit.  Sides at the edges of the strips of 62 columns and bands of
+16 and 32 rows; sums, time blocks and graphs between the passes; ensembles;
+the step of an error."""
+import numpy as np
+import pytest
+
+from paper_1204_6734_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# 62 columns a strip: full, one more, one less; one strip only; 32 rows a band
+SIDES = [(2976, 2944), (2977, 2945), (3037, 2927), (62, 141001), (8191, 4129)]
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2])
+@pytest.mark.parametrize("nx,ny", SIDES)
+def test_two_steps_a_pass_equal_single_steps(flb, nx, ny, basis):
+    kw = dict(precision=flb.FP32_SHIFTED, basis=basis, ux0=0.1, uy0=-0.03, seed=nx,
+              kT=0.0 if basis == 1 and nx == 62 else 1e-4, init=flb.INIT_THERMAL,
+              tau=I.mixed_taus(2))
+    a = flb.Lattice(flb.make_params(nx, ny, **kw))
+    b = flb.Lattice(flb.make_params(nx, ny, **kw))
+    b.set_launch(1, 0)
+    for n in (4, 7, 9):
+        a.step(n)
+        b.step(n)
+    np.testing.assert_array_equal(a.populations(), b.populations())
+
+
+@pytest.mark.parametrize("every,block", [(5, 7), (12, 24)])
+def test_sums_and_graphs_between_passes(flb, every, block):
+    kw = dict(precision=flb.FP32_SHIFTED, ux0=0.1, kT=1e-4, seed=5, sample_every=every,
+              block_steps=block)
+    a, b, g = (flb.Lattice(flb.make_params(3000, 2950, **kw)) for _ in range(3))
+    b.set_launch(1, 0)
+    g.set_graph_chunk(20)
+    for n in (21, 43, 60):
+        for L in (a, b, g):
+            L.step(n)
+        want = b.covariance()
+        for L in (a, g):
+            for k, v in L.covariance().items():
+                np.testing.assert_array_equal(v, want[k], err_msg=k)
+    want = b.populations()
+    np.testing.assert_array_equal(a.populations(), want)
+    np.testing.assert_array_equal(g.populations(), want)
+
+
+def test_ensemble_members_equal_lattices(flb):
+    ps = [flb.make_params(1003, 1001, precision=flb.FP32_SHIFTED, ux0=0.01 * m, kT=1e-4,
+                          seed=m + 1, sample_every=6 if m % 2 else 0, block_steps=12)
+          for m in range(9)]
+    e = flb.Ensemble(ps)
+    e.step(33)
+    for m in (0, 5, 8):
+        L = flb.Lattice(ps[m])
+        L.set_launch(1, 0)
+        L.step(33)
+        np.testing.assert_array_equal(e.populations(m), L.populations())
+
+
+@pytest.mark.parametrize("kT", [0.01, 0.015, 0.02, 0.05])
+def test_an_error_has_the_same_step(flb, kT):
+    kw = dict(precision=flb.FP32_SHIFTED, kT=kT, seed=7, init=flb.INIT_THERMAL)
+    a = flb.Lattice(flb.make_params(3000, 2950, **kw))
+    b = flb.Lattice(flb.make_params(3000, 2950, **kw))
+    b.set_launch(1, 0)
+    codes = []
+    for L in (a, b):
+        L.step(40)
+        try:
+            L.sync()
+            codes.append(0)
+        except flb.FlbError as e:
+            codes.append(e.code)
+    assert codes[0] == codes[1]
+    assert a.error_step == b.error_step
+    assert kT < 0.05 or codes[0] == flb.E_INVALID_VELOCITY
