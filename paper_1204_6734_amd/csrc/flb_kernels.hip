@@ -776,6 +776,20 @@ hipError_t launch_close_block_many(double* const* partials, double* const* recor
   return close_block_sums_many<kNStat>(partials, records, record_offset, n, ntiles, st);
 }
 
+hipError_t launch_close_block_list(double* const* partials, double* const* records,
+                                   const int* ntiles, int n, hipStream_t st) {
+  for (int i = 0; i < n; i += kCloseList) {
+    const int m = std::min(kCloseList, n - i);
+    CloseList L{};
+    std::copy_n(partials + i, m, L.partials);
+    std::copy_n(records + i, m, L.record);
+    std::copy_n(ntiles + i, m, L.ntiles);
+    const hipError_t e = close_block_sums_list<kNStat>(L, m, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_merge_blocks(double* rec, int nhalf, hipStream_t st) {
   hipLaunchKernelGGL(merge_blocks_kernel, dim3(1), dim3(64), 0, st, rec, nhalf);
   return hipGetLastError();

@@ -49,7 +49,10 @@ __device__ __forceinline__ void fold_tiles(double* partials, int ntiles, int chu
 }
 
 // Ranges of stage one: at most kFoldRows workgroups of at least one tile.
-inline void fold_ranges(int ntiles, int* chunk, int* nranges) {
+// Ranges of one tile each (up to kFoldRows tiles) are their own sums: stage
+// two reads the partials themselves and stage one, which would write each sum
+// over itself, is not launched.
+__host__ __device__ inline void fold_ranges(int ntiles, int* chunk, int* nranges) {
   const int c = ntiles > kFoldRows ? (ntiles + kFoldRows - 1) / kFoldRows : 1;
   *chunk = c;
   *nranges = (ntiles + c - 1) / c;
@@ -120,6 +123,31 @@ __global__ __launch_bounds__(1024) void gather_folds_many_kernel(double* const* 
   gather_folds<NSTAT>(partials[blockIdx.y], nranges, chunk, records[blockIdx.y] + record_offset);
 }
 
+// And for lattices of any tile counts, listed in the kernel's arguments (a
+// server's requests that close at the same step).
+constexpr int kCloseList = 32;
+struct CloseList {
+  double* partials[kCloseList];
+  double* record[kCloseList];
+  int ntiles[kCloseList];
+};
+
+template <int NSTAT>
+__global__ __launch_bounds__(1024) void fold_tiles_list_kernel(const CloseList L) {
+  const int ntiles = L.ntiles[blockIdx.y];
+  int chunk = 1, nranges = 1;
+  fold_ranges(ntiles, &chunk, &nranges);
+  if (chunk == 1 || (int)blockIdx.x >= nranges) return;
+  fold_tiles<NSTAT>(L.partials[blockIdx.y], ntiles, chunk);
+}
+
+template <int NSTAT>
+__global__ __launch_bounds__(1024) void gather_folds_list_kernel(const CloseList L) {
+  int chunk = 1, nranges = 1;
+  fold_ranges(L.ntiles[blockIdx.y], &chunk, &nranges);
+  gather_folds<NSTAT>(L.partials[blockIdx.y], nranges, chunk, L.record[blockIdx.y]);
+}
+
 // Open sums (partials left as they are): workgroup b sums tiles
 // [b chunk, min((b+1) chunk, n)) into row b of out, lanes as above.
 template <int NSTAT>
@@ -153,10 +181,12 @@ hipError_t close_block_sums(double* partials, int ntiles, double* record, hipStr
   if (ntiles <= 0) return hipErrorInvalidValue;
   int chunk = 1, nranges = 1;
   fold_ranges(ntiles, &chunk, &nranges);
-  hipLaunchKernelGGL(fold_tiles_kernel<NSTAT>, dim3(nranges), dim3(1024), 0, st, partials,
-                     ntiles, chunk);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (chunk > 1) {
+    hipLaunchKernelGGL(fold_tiles_kernel<NSTAT>, dim3(nranges), dim3(1024), 0, st, partials,
+                       ntiles, chunk);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(gather_folds_kernel<NSTAT>, dim3(1), dim3(1024), 0, st,
                      partials, nranges, chunk, record);
   return hipGetLastError();
@@ -171,12 +201,34 @@ hipError_t close_block_sums_many(double* const* partials, double* const* records
   if (ntiles <= 0 || n <= 0) return hipErrorInvalidValue;
   int chunk = 1, nranges = 1;
   fold_ranges(ntiles, &chunk, &nranges);
-  hipLaunchKernelGGL(fold_tiles_many_kernel<NSTAT>, dim3(nranges, n), dim3(1024), 0, st,
-                     partials, ntiles, chunk);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (chunk > 1) {
+    hipLaunchKernelGGL(fold_tiles_many_kernel<NSTAT>, dim3(nranges, n), dim3(1024), 0, st,
+                       partials, ntiles, chunk);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(gather_folds_many_kernel<NSTAT>, dim3(1, n), dim3(1024), 0,
                      st, partials, nranges, chunk, records, record_offset);
+  return hipGetLastError();
+}
+
+// For the first n <= kCloseList lattices of a list.
+template <int NSTAT>
+hipError_t close_block_sums_list(const CloseList& L, int n, hipStream_t st) {
+  if (n <= 0 || n > kCloseList) return hipErrorInvalidValue;
+  int most = 0;
+  for (int i = 0; i < n; ++i) {
+    if (L.ntiles[i] <= 0) return hipErrorInvalidValue;
+    int chunk = 1, nranges = 1;
+    fold_ranges(L.ntiles[i], &chunk, &nranges);
+    if (chunk > 1) most = std::max(most, nranges);
+  }
+  if (most) {
+    hipLaunchKernelGGL(fold_tiles_list_kernel<NSTAT>, dim3(most, n), dim3(1024), 0, st, L);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(gather_folds_list_kernel<NSTAT>, dim3(1, n), dim3(1024), 0, st, L);
   return hipGetLastError();
 }
 

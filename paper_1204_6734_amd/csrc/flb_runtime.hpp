@@ -109,6 +109,9 @@ hipError_t launch_close_block(double* partials, int ntiles, double* record, hipS
 // and record bases; the record written at records[k] + record_offset)
 hipError_t launch_close_block_many(double* const* partials, double* const* records,
                                   size_t record_offset, int n, int ntiles, hipStream_t st);
+// n lattices of any tile counts (host arrays)
+hipError_t launch_close_block_list(double* const* partials, double* const* records,
+                                   const int* ntiles, int n, hipStream_t st);
 hipError_t launch_merge_blocks(double* rec, int nhalf, hipStream_t st);
 // folds: kFoldRows rows of kNStat doubles of scratch
 hipError_t launch_open_sum(const double* partials, int ntiles, double* out, double* folds,

@@ -337,6 +337,12 @@ int flb_server::run_chunk() {
     HIPC(hipStreamWaitEvent(st2, forked, 0));
   }
   const int storage = cfg.precision == 0 ? 0 : 1;
+  // Time blocks that end at a step, the requests of a stream in one pair of
+  // launches.  Twelve requests (sides 93 to 980, a block every 50 steps): 137
+  // pairs of 15 us became 38 of 25, half of them beside the other stream's
+  // steps; 27.4 -> 26.2 ms in all.
+  std::vector<double*> partials[2], records[2];
+  std::vector<int> ntiles[2];
   for (int k = 0; k < K; ++k) {
     for (const Half& h : halves) {
       // the sampling variant only where some request of the half samples
@@ -351,14 +357,31 @@ int flb_server::run_chunk() {
                        d_prefix[h.cls] + h.prefix_at, h.count, h.tiles, d_clock, (uint32_t)k,
                        LaunchCfg{}, h.q));
     }
+    for (int q = 0; q < 2; ++q) {
+      partials[q].clear();
+      records[q].clear();
+      ntiles[q].clear();
+    }
     for (size_t i = 0; i < active.size(); ++i) {
       Active& a = active[i];
       const uint64_t own = a.desc.t0 + clock + (uint64_t)k;
       if (own >= a.nsteps || a.p.sample_every <= 0) continue;
       if (own % (uint64_t)a.p.sample_every != 0) continue;
+      if (a.stats.plain_close_next()) {
+        const int q = stream_of[i] == st2;
+        const uint64_t b = a.stats.close_counted((uint64_t)a.p.nx * a.p.ny);
+        partials[q].push_back(a.desc.partials);
+        records[q].push_back(records_of(a, arena, cfg.precision) + b * kNStat);
+        ntiles[q].push_back(a.desc.ntiles);
+        continue;
+      }
       HIPC(a.stats.after_sample((uint64_t)a.p.nx * a.p.ny, a.desc.partials, a.desc.ntiles,
                                 records_of(a, arena, cfg.precision), stream_of[i]));
     }
+    for (int q = 0; q < 2; ++q)
+      if (!ntiles[q].empty())
+        HIPC(launch_close_block_list(partials[q].data(), records[q].data(), ntiles[q].data(),
+                                     (int)ntiles[q].size(), q ? st2 : st));
   }
   if (two) {
     HIPC(hipEventRecord(joined, st2));

@@ -34,3 +34,30 @@ def test_sums_of_every_tile_count(flb, tiles, block):
         assert np.abs(c["mean_df"] - mean).max() <= 1e-11 * np.sqrt(cov.max())
         assert np.abs(c["cov_f"] - cov).max() <= 1e-11 * cov.max()
     L.close()
+
+
+def test_requests_that_close_together(flb):
+    """More requests than one launch lists, of tile counts on both sides of
+    one range per tile, closing at the same steps and at their own: each
+    request's correlators are its lattice's."""
+    ps = []
+    for k in range(70):
+        tiles = [1, 5, 255, 256, 257, 300, 600][k % 7]
+        ps.append(flb.make_params(50 + k % 5, 4 * tiles - 1, ux0=0.3 if k % 9 == 4 else 0.05,
+                                  kT=1e-4, seed=k, sample_every=1 + k % 2,
+                                  block_steps=3 + (k % 10 == 9)))
+    S = flb.Server(256 << 20, max_slots=70, chunk_steps=8, threaded=False)
+    for k, p in enumerate(ps):
+        S.submit(p, 30, tag=k)
+    S.drain()
+    res = {r["tag"]: r for r in S.poll(80)}
+    S.close()
+    assert len(res) == len(ps)
+    for k, p in enumerate(ps):
+        L = flb.Lattice(p)
+        L.step(30)
+        want, got = L.covariance(), res[k]["cov"]
+        L.close()
+        assert got["nblocks"] == want["nblocks"] > 0
+        for key in ("mean_df", "cov_f", "se_cov_f"):
+            np.testing.assert_array_equal(got[key], want[key], err_msg="%d %s" % (k, key))
