@@ -429,24 +429,34 @@ void Group::plan_multi(int cus) {
 
 // Rows a wavefront of step_march_kernel takes, 0 where one step per launch is
 // the better one.  Two steps per pass over memory halve the traffic and cost
-// (64/62)(1 + 1/H) of the arithmetic, so they pay where the populations do not
-// stay in the 256 MiB last-level cache and the arithmetic is the FP32 one (FP64
-// is bound by it).  us a step, one step per launch -> this kernel: 2560^2 (225
-// MiB) 71 -> 78, 2003x4001 (275) 95.5 -> 96.4, 512x16384 (288) 100 -> 101,
-// 2900^2 (289) 105 -> 100, 3072^2 (324) 116 -> 107, 4096^2 214 -> 189, 8192^2
-// 845 -> 717.  Narrow members waste lanes of their last strip: 200^2 x 256 (78 %
+// (64/62)(1 + 1/H) of the arithmetic, so they pay where the FP32 arithmetic is
+// the smaller part: never in FP64, in the Hermite basis where the populations
+// exceed the 32 MiB of the XCDs' L2 caches, in the others (twice the
+// arithmetic) where they exceed the 256 MiB last-level cache.  us a step, one
+// step per launch -> this kernel:
+//   f-norm   2560^2 (225 MiB) 71 -> 78, 2003x4001 (275) 95.5 -> 96.4, 2900^2
+//            (289) 105 -> 100, 3072^2 (324) 116 -> 107, 8192^2 845 -> 694
+//   Hermite  1003x601 (21) 7.7 -> 8.1, 1024^2 (36) 13.8 -> 11.3, 2048^2 43.8 ->
+//            33.9, 8192^2 826 -> 507
+// Narrow members waste lanes of their last strip (f-norm): 200^2 x 256 (78 %
 // used) 160 -> 138, 256^2 x 256 (80 %) 223 -> 211, 128^2 x 1000 (67 %) 217 ->
-// 239.  32 rows once that is four rounds of the 16 wavefronts a compute unit
-// holds (8192^2 727 -> 717, 512^2 x 128 389 -> 384), 16 below (4096^2 191 ->
-// 189, 2816^2 92 -> 91).
+// 239.  Rows: more share the first and last among themselves, fewer keep more
+// wavefronts in flight and the rows of neighbouring bands in the cache.  f-norm:
+// 32 once that is four rounds of the 16 wavefronts a compute unit holds (8192^2
+// 703 -> 694), 16 below (4096^2 187 -> 183, 2816^2 92 -> 91).  Hermite: 8 once
+// that is one round (8192^2: 529, 507, 544 at 4, 8, 16; 1536^2: 19.7, 18.4,
+// 21.9), 4 below (1024^2: 11.3, 12.3).
 int Group::plan_march(int cus) const {
   const int nx = P[0].nx, ny = P[0].ny, n = (int)P.size();
   if (storage != 1 || compute != 1) return 0;
-  if ((double)nx * ny * n * 36.0 < (double)((size_t)300 << 20)) return 0;
+  const bool hermite = basis == FLB_BASIS_HERMITE;
+  const double bytes = (double)nx * ny * n * 36.0, mib = 1 << 20;
+  if (bytes < (hermite ? 32 : 300) * mib) return 0;
   const int strips = (nx + kMarchCols - 1) / kMarchCols;
   if (4 * nx < 3 * 64 * strips) return 0;
-  const double waves = (double)strips * ((ny + 31) / 32) * n;
-  return waves >= 64.0 * cus ? 32 : 16;
+  const int rows = hermite ? 8 : 32;
+  const double waves = (double)strips * ((ny + rows - 1) / rows) * n;
+  return waves >= (hermite ? 16.0 : 64.0) * cus ? rows : rows / 2;
 }
 
 // Whether a second population buffer of this size is taken: small ones always,

@@ -16,11 +16,16 @@
 // kernel's bit for bit.  Source and destination are two buffers, as in
 // flb_multi.hip.
 //
-// Measured: 8192^2, us a step 845 -> 717 (79.4 -> 93.6 GLUPS), 4096^2 214 ->
-// 189, 16384^2 3430 -> 2890.  Bound by FP32 arithmetic, as lattices that fit
-// the cache are (2560^2: 92.6 GLUPS in one step per launch).  101 vector
-// registers leave four wavefronts a SIMD; five spill (8192^2: 883 us).  The row
-// of loads for the next site is in flight while this one's two steps compute.
+// Measured, us a step, one step per launch -> this kernel: f-norm basis 8192^2
+// 845 -> 694 (79.4 -> 96.7 GLUPS), 4096^2 215 -> 183; Hermite basis 8192^2 826
+// -> 507 (132 GLUPS), 4096^2 212 -> 135, 2048^2 43.8 -> 33.9, 1536^2 26.3 ->
+// 18.4.  Bound by FP32 arithmetic in the f-norm basis (lattices that fit the
+// cache reach 92.6 GLUPS in one step per launch); 101 vector registers leave
+// four wavefronts a SIMD, five spill (8192^2: 883 us).  The row of loads for the
+// next site is in flight while this one's two steps compute.  The barrier of
+// each row gives 1 % there and 13 % in the Hermite basis (8192^2, 8 rows: 585 ->
+// 507); workgroups of eight wavefronts gain 2 % more at 8192^2 in the Hermite
+// basis and lose 5 % in the f-norm basis and below 2048^2.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -75,7 +80,7 @@ __global__ __launch_bounds__(256) void step_march_kernel(const SlotDesc* __restr
   const int band = (int)(((uint64_t)w * M.st_magic) >> M.st_shift);
   const int strip = (int)w - band * M.strips;
   const int nx = M.nx, ny = M.ny, y0 = band * M.H, H = min(M.H, ny - y0);
-  if (H <= 0) return;
+  const int rows = H > 0 ? H + 2 : 0;
   const SlotDesc& sd = slots[slot];
   const uint64_t t = sd.t0 + *clock + step_idx;
   const int lane = threadIdx.x & 63;
@@ -94,12 +99,17 @@ __global__ __launch_bounds__(256) void step_march_kernel(const SlotDesc* __restr
 
   int y = y0 == 0 ? ny - 1 : y0 - 1;
   float next[9];
-  load_row(src, M.pitch, y, voff, next);
+  if (rows) load_row(src, M.pitch, y, voff, next);
   // what the first step left for rows above: of the row above (0, 1, 3) and of
   // the two above (2, 5, 6), each already moved along x
   float a0 = 0.f, a1 = 0.f, a3 = 0.f, b2 = 0.f, b5 = 0.f, b6 = 0.f, c2 = 0.f, c5 = 0.f, c6 = 0.f;
 #pragma unroll 1
-  for (int j = 0; j < H + 2; ++j) {
+  for (int j = 0; j < M.H + 2; ++j) {
+    // neighbouring strips in step (every wavefront of the workgroup comes here
+    // M.H + 2 times; nothing is exchanged): their rows share cache lines at the
+    // strips' edges, which leave the cache half written when one runs ahead
+    __builtin_amdgcn_s_barrier();
+    if (j >= rows) continue;
     float h[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) h[i] = next[i];

@@ -1,7 +1,7 @@
 """Two steps per pass over memory (FP32 lattices larger than the last-level
 cache) against one step per launch, which a forced launch shape selects: the
 same bit for bit.  Sides at the edges of the strips of 62 columns and bands of
-16 and 32 rows; sums, time blocks and graphs between the passes; ensembles;
+4 to 32 rows; sums, time blocks and graphs between the passes; ensembles;
 the step of an error."""
 import numpy as np
 import pytest
@@ -12,10 +12,12 @@ pytestmark = pytest.mark.gpu
 
 # 62 columns a strip: full, one more, one less; one strip only; 32 rows a band
 SIDES = [(2976, 2944), (2977, 2945), (3037, 2927), (62, 141001), (8191, 4129)]
+# the Hermite basis takes bands of 4 and 8 rows, and smaller lattices
+HERMITE = [(992, 942), (993, 943), (1053, 1001), (1551, 1553)]
 
 
-@pytest.mark.parametrize("basis", [0, 1, 2])
-@pytest.mark.parametrize("nx,ny", SIDES)
+@pytest.mark.parametrize("nx,ny,basis", [(x, y, b) for x, y in SIDES for b in (0, 1, 2)] +
+                         [(x, y, 1) for x, y in HERMITE])
 def test_two_steps_a_pass_equal_single_steps(flb, nx, ny, basis):
     kw = dict(precision=flb.FP32_SHIFTED, basis=basis, ux0=0.1, uy0=-0.03, seed=nx,
               kT=0.0 if basis == 1 and nx == 62 else 1e-4, init=flb.INIT_THERMAL,
