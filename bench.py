@@ -18,8 +18,9 @@ the board's power limit settles the step at.
 
 Prints one JSON line: MLUPS (lattice-site updates per second / 1e6) over
 the timed steps, the step kernel's achieved HBM bandwidth against the
-8 TB/s peak (72 algorithmic bytes per site update: nine FP32 reads and nine
-FP32 writes in place), a served-requests measurement (solves/s and p50/p99
+8 TB/s peak (36 bytes per site update, the populations being read and
+written once for two steps; pct_hbm_roofline is against the rate that 72
+bytes, one pass per step, allow), a served-requests measurement (solves/s and p50/p99
 latency of mixed Poisson-arriving requests through the continuous-batching
 server, next to the plain FP64 one-lattice-per-launch path on the same
 arrivals), and the FP64 CPU oracle's rate on a bounded sample of the
@@ -43,19 +44,22 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_SITE = {"f32": 72, "f64": 144}
 # D3Q19 FP32 f-norm step: VALU wavefront instructions per wavefront (= per
-# site), SQ_INSTS_VALU / SQ_WAVES averaged over both phases,
+# site), counted in its gfx950 code and averaged over both phases,
 # profiles/step3_fp32_256cube_d3q19.md
-D3Q19_VALU_PER_SITE = 2095
-# FP32 floating-point operations per site of that kernel (its variant for
+D3Q19_VALU_PER_SITE = 1950
+# the same of the two-step pass of the large D2Q9 FP32 lattice, per 64 site
+# updates (halo lanes and rows included), profiles/step_fp32_8192_counters.md
+MARCH_VALU_PER_SITE = 418.5
+# FP32 floating-point operations per site of that D3Q19 kernel (its variant for
 # one relaxation time, which this workload's tau = 1 selects), counted in its
-# gfx950 code: FMAs 2 each (1519 v_fma/v_fmac/v_fmamk), multiplies, adds and
+# gfx950 code: FMAs 2 each (1348 v_fma/v_fmac/v_fmamk), multiplies, adds and
 # subtracts 1 each (225 + 85), transcendentals (rsq, rcp, sqrt, log, sin,
 # cos) 1 each (48); conversions, compares and min/max are not counted.  One
 # lane computes one site.
-D3Q19_FLOPS_PER_SITE = 3396
-# the same for the FP64 kernel of that workload: 1804 FMAs, 327 multiplies,
+D3Q19_FLOPS_PER_SITE = 3054
+# the same for the FP64 kernel of that workload: 1630 FMAs, 327 multiplies,
 # 117 adds and subtracts, 33 transcendentals (FP64 operations)
-D3Q19_FP64_FLOPS_PER_SITE = 4085
+D3Q19_FP64_FLOPS_PER_SITE = 3737
 # FP32 vector peak without packed (two-wide) instructions, which this
 # library does not use: 256 CUs x 4 SIMDs x 16 lanes x 2 (FMA) x 2.4 GHz;
 # the FP64 vector peak is the same
@@ -68,7 +72,9 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 KERNEL_SOURCES = ["paper_1204_6734_amd/csrc/flb_device.hpp",
                   "paper_1204_6734_amd/csrc/fp64_series.hpp",
                   "paper_1204_6734_amd/csrc/flb_buffer.hpp",
+                  "paper_1204_6734_amd/csrc/flb_correlate.hpp",
                   "paper_1204_6734_amd/csrc/flb_step.hip",
+                  "paper_1204_6734_amd/csrc/flb_march.hip",
                   "paper_1204_6734_amd/csrc/flb_kernels.hpp"]
 
 
@@ -87,7 +93,7 @@ def kernel_hash() -> str:
 
 
 def traffic_from_profiles(name: str):
-    """HBM bytes per launch from the committed counter summary, if it was
+    """HBM bytes per launch (two steps, where a pass takes two) from the committed counter summary, if it was
     taken on the current kernel sources."""
     path = os.path.join(ROOT, "profiles", f"{name}_traffic.json")
     if not os.path.exists(path):
@@ -219,8 +225,8 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
     settle = F.Lattice(F.make_params(nx, nx, precision=p.precision, basis=bcode, rho0=1.0,
                                      ux0=ux0, kT=1e-4, seed=2, sample_every=sample_every,
                                      block_steps=p.block_steps), stream=stream)
-    lc = L.get_launch()
-    settle.set_launch(lc["tiles_per_block"], lc["grid_blocks"])
+    if launch is not None:  # otherwise the shape just tuned is the settling lattice's too
+        settle.set_launch(*launch)
     settle_steps = min(20000, max(20, int(round(300.0 / probes["copy_ms"]))))
 
     def run(n):
@@ -250,6 +256,10 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
     kms, launches = L.kernel_time()
     L.profile(False)
     sites = nx * nx
+    # large FP32 lattices take two steps per pass over memory between samples,
+    # unless --launch fixes the shape of one-step launches (Group::plan_march)
+    two = (fp32 and launch is None and sample_every == 0 and
+           36 * sites >= (32 if basis == "hermite" else 300) << 20)
     # structure-factor samples and mode logs that fell in the timed steps
     n_sk = (len([t for t in range(tw0, tw0 + steps) if t % every == 0]) if every > 0 else 0)
     with_sk = None
@@ -269,7 +279,7 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
         with_sk = {"steps": every, "sk_samples": 1, "mode_logs": 1,
                    "ms_per_step": round(dt1 * 1e3 / every, 4),
                    "mlups": round(sites * every / dt1 / 1e6, 1)}
-    return {"sites": sites, "dt": dt, "kernel_ms": kms / max(launches, 1), "launches": launches,
+    return {"sites": sites, "dt": dt, "steps_per_pass": 2 if two else 1, "kernel_ms": kms / max(launches, 1), "launches": launches,
             "mode_log": [abs(z) for z in log[-3:]], "probes": probes, "settle_steps": settle_steps,
             "sk_in_window": n_sk, "mode_logs_in_window": len(log), "with_sk": with_sk,
             "launch": {"chosen": L.get_launch(), "candidates": tune},
@@ -289,7 +299,7 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
                        "parallelism": "single GPU"},
             "dtype": "f32" if fp32 else "f64",
             # FP32 storage computes the collision in FP64 above |u0| = 0.25
-            "kernel_label": "step_kernel<%s,%s>" % (
+            "kernel_label": "step_march_kernel<%s>" % bname if two else "step_kernel<%s,%s>" % (
                 ("float,float" if abs(ux0) <= 0.25 else "float,double") if fp32
                 else "double,double", bname) +
                 (f" (correlator-sampling variant every {sample_every} steps)"
@@ -563,7 +573,9 @@ def main():
                   sample_every=args.sample_every)
     mlups = r["sites"] * args.steps / r["dt"] / 1e6
     bps = BYTES_PER_SITE[r["dtype"]]
-    achieved = bps * r["sites"] / (r["kernel_ms"] * 1e-3) / 1e9
+    # bytes a step moves: a pass of two steps reads and writes once
+    moved = bps // r["steps_per_pass"]
+    achieved = moved * r["sites"] / (r["kernel_ms"] * 1e-3) / 1e9
     traffic = traffic_from_profiles(r["kernel_name"])
     # the step's memory traffic with no arithmetic (same layout, tiles and
     # addressing): the practical ceiling of its access pattern; and a plain
@@ -578,10 +590,12 @@ def main():
         "warmup": args.warmup, "ms_per_step": round(r["dt"] * 1e3 / args.steps, 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": r["dtype"],
         "data": "synthetic", "config": r["config"],
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm" if r["steps_per_pass"] == 1 else "alu",
+                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "kernel": r["kernel_label"],
-                     "bytes_per_site": bps, "kernel_ms": round(r["kernel_ms"], 4),
+                     "bytes_per_site": moved, "steps_per_pass": r["steps_per_pass"],
+                     "kernel_ms": round(r["kernel_ms"], 4),
                      "launches": r["launches"],
                      "copy_probe": {"GBps": round(copy_gbps, 1), "ms": round(copy_ms, 4),
                                     "frac_of_peak": round(copy_gbps / HBM_PEAK_GBS, 4),
@@ -597,6 +611,10 @@ def main():
                              "mode_logs_in_window": r["mode_logs_in_window"],
                              "with_sk": r["with_sk"]},
     }
+    if r["steps_per_pass"] == 2 and args.basis == "fnorm":
+        instr = MARCH_VALU_PER_SITE * r["sites"] / 64
+        out["valu_issue"] = {"wavefront_instructions_per_site": MARCH_VALU_PER_SITE,
+                             "issue_ms_at_4_cycles": round(instr / VALU_ISSUE_PEAK * 1e3, 4)}
     if not args.no_serving:
         out["serving"] = run_serving(F, torch, nreq=args.requests or 40)
     if not args.no_cpu_baseline:

@@ -195,7 +195,8 @@ int64_t flb_lattice_error_step(flb_lattice* L);
 
 /* Device time of the step kernels enqueued since the last reset, measured
  * with HIP events around each launch (enable first; adds two events per
- * launch). */
+ * launch); `launches` counts one per step, also where a launch takes several
+ * (see launch shape). */
 int flb_lattice_profile(flb_lattice* L, int32_t on);
 int flb_lattice_kernel_time(flb_lattice* L, double* ms, uint64_t* launches);
 
@@ -267,10 +268,11 @@ int flb_lattice_population_buffer(flb_lattice* L, void** dev, size_t* bytes, uin
 
 /* ------------------------------------------------------------- ensembles
  * n replicas of one lattice shape (same nx, ny, precision, basis), each with
- * its own rho0, u0, kT, tau, seed and sampling, advanced by one batched
- * kernel launch per step (two when some FP32 replicas have |u0| > 0.25 and
- * need the FP64 collision: those form their own launch); chunks of steps are
- * replayed from a captured hipGraph.  Replica results are bit-identical to
+ * its own rho0, u0, kT, tau, seed and sampling, advanced by batched kernel
+ * launches (one per step, or per several steps as below; FP32 replicas with
+ * |u0| > 0.25, which need the FP64 collision, form their own); chunks of
+ * steps are replayed from a captured hipGraph, in which two halves of many
+ * replicas advance side by side.  Replica results are bit-identical to
  * running each alone. */
 typedef struct flb_ensemble flb_ensemble;
 int flb_ensemble_create(const flb_params* per_replica, int32_t n, void* hip_stream,
@@ -292,7 +294,9 @@ void flb_ensemble_destroy(flb_ensemble* E);
 /* ------------------------------------------------------------ launch shape
  * The batched step works on tiles of 256 sites, four 64-lane wavefronts:
  * 256 x 1 (the four along one lattice row) on lattices at least 256 sites
- * wide, 64 x 4 (one per tile row) on narrower ones.  Its launch shape is a
+ * wide, 64 x 4 (one per tile row) on narrower ones, on FP32 lattices of up to
+ * 65536 sites, and where the last 256 x 1 tile of a row would be mostly empty
+ * (FP32 lattices and unsampled FP64 ones).  Its launch shape is a
  * tuning choice that never changes a
  * result: every shape computes bit-identical populations and correlator
  * sums (each tile forms its partial sums in the same order).
@@ -305,6 +309,15 @@ void flb_ensemble_destroy(flb_ensemble* E);
  * Steps that sample correlators or structure-factor fields always give each
  * tile group its own workgroup, and they and every step computed in FP64
  * take at most 2 tiles per workgroup (a larger value is lowered to 2).
+ * Two kinds of lattices and ensembles take several steps per launch where
+ * the populations' memory is the library's own: small ones (up to one tile per
+ * compute unit in FP32, narrow ones also in FP64), up to six steps with the
+ * populations in the workgroups' LDS; and FP32 ones larger than the caches
+ * (300 MiB of populations, 32 MiB in the Hermite basis), two steps per pass
+ * over memory.  They write to a second population buffer, which a lattice
+ * above 256 MiB takes only where seven eighths of the device's memory stay
+ * free; otherwise, and after flb_*_set_launch, each launch is one step.
+ * Results are the same bit for bit.
  * A new lattice or ensemble starts with {1, 0}, or with the shape an earlier
  * autotune in this process chose for the same device, precision, basis and
  * tile count. */
@@ -329,8 +342,9 @@ int flb_lattice_autotune(flb_lattice* L, int32_t reps, flb_launch_config* result
                          int32_t max_results, int32_t* n_results);
 int flb_ensemble_autotune(flb_ensemble* E, int32_t reps, flb_launch_config* results,
                           int32_t max_results, int32_t* n_results);
-/* Force a shape (FLB_E_ARG for tiles_per_block not in {1, 2, 4} or a
- * negative grid_blocks or one that is not a multiple of 8). */
+/* Force a shape, and one step per launch until the next autotune (FLB_E_ARG
+ * for tiles_per_block not in {1, 2, 4} or a negative grid_blocks or one that
+ * is not a multiple of 8). */
 int flb_lattice_set_launch(flb_lattice* L, const flb_launch_config* c);
 int flb_ensemble_set_launch(flb_ensemble* E, const flb_launch_config* c);
 int flb_lattice_get_launch(flb_lattice* L, flb_launch_config* c);
@@ -396,7 +410,8 @@ void flb3_lattice_destroy(flb3_lattice* L);
  * Continuous batching of simulation requests of mixed size, temperature and
  * background velocity.  Requests wait in FIFO order; one is admitted as soon
  * as a slot is free and its device footprint fits the memory budget; all
- * admitted requests advance together, one batched launch per step, in
+ * admitted requests advance together, one batched launch per step and half
+ * of the requests (the halves side by side on two streams), in
  * chunks of `chunk_steps`; finished requests leave at chunk boundaries and
  * free their slot and memory for the next.  A request's result equals the
  * result of running it alone (noise keyed by its own seed, step and site;

@@ -405,6 +405,16 @@ uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
 // collisions gain on those only (21^2 3.7 -> 2.5 / 4.9 -> 3.5, 32^2 3.6 -> 3.1
 // / 4.9 -> 4.2; 64^2 3.7 -> 3.9 / 4.9 -> 5.5): their halo costs more than the
 // launches saved.
+// A program may step several lattices side by side, each on its own stream,
+// and the recomputed halo then takes time from the others once they fill the
+// chip together: so the wavefronts of a launch are bounded by what three side
+// by side still gain with, and a launch takes fewer steps, or one, above that.
+// Three FP32 lattices, us a step of all: 256^2 plain 4.2 one step a launch, 4.3
+// two (7 wavefronts a CU), 6.6 four (11); with sums 256 x 128 6.3 -> 5.7, 256 x
+// 160 9.7 -> 10.5, 256^2 6.9 -> 10.0; 24 x 32^2 with sums 5.2 -> 4.8 (8.3
+// wavefronts a CU), 32 x 32^2 5.3 -> 6.4 (11); FP64 16 x 32^2 4.8 -> 4.2 (4.5),
+// 40 x 21^2 5.3 -> 4.1 two steps (3.8), 6.4 four (6.6), 32 x 32^2 5.5 -> 6.5
+// two (5), 8.3 four (9).
 void Group::plan_multi(int cus) {
   multi_max = 0;
   std::fill(&multi_nt[0][0], &multi_nt[0][0] + 2 * (kMultiMaxSteps + 1), 0);
@@ -420,11 +430,15 @@ void Group::plan_multi(int cus) {
   if (total_tiles > (narrow && compute == 1 ? 2 * cus : cus)) return;
   const int most = narrow && compute == 1 && total_tiles <= cus ? 6 : 4;
   for (int sample = 0; sample < 2; ++sample)
-    for (int K = 2; K <= most; K += 2)
-      if (multi_fits(storage, compute, sample != 0, nx, K, 1, max_lds)) {
-        multi_nt[sample][K] = 1;
-        multi_max = std::max(multi_max, K);
-      }
+    for (int K = 2; K <= most; K += 2) {
+      if (!multi_fits(storage, compute, sample != 0, nx, K, 1, max_lds)) continue;
+      const double waves = (double)total_tiles * multi_waves(compute, sample != 0, nx, K, 1);
+      if (sample && !narrow ? 2 * total_tiles > cus
+                            : waves > (compute == 0 ? 4.9 : sample ? 8.3 : 7.0) * cus)
+        continue;
+      multi_nt[sample][K] = 1;
+      multi_max = std::max(multi_max, K);
+    }
 }
 
 // Rows a wavefront of step_march_kernel takes, 0 where one step per launch is

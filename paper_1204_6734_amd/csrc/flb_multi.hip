@@ -414,7 +414,7 @@ static int drawing_waves(int compute, int nx, int K, int nt) {
 }
 // All wavefronts of a workgroup: those that draw and those that sum are the
 // same ones where they would not fit side by side.
-static int multi_waves(int compute, bool sample, int nx, int K, int nt) {
+int multi_waves(int compute, bool sample, int nx, int K, int nt) {
   const int most = (compute == 0 ? multi_max_threads<double>() : multi_max_threads<float>()) / 64;
   const int nc = colliding_waves(nx, K, nt), nd = drawing_waves(compute, nx, K, nt);
   if (!sample) return nc + nd;

@@ -18,6 +18,8 @@ constexpr int multi_max_threads() {
 
 // Whether K steps of nt stacked tiles per workgroup fit the kernel's limits.
 bool multi_fits(int storage, int compute, bool sample, int nx, int K, int nt, size_t max_lds);
+// Wavefronts of a workgroup of nt tiles that takes K steps.
+int multi_waves(int compute, bool sample, int nx, int K, int nt);
 // Allow the kernels the LDS that up to K steps of one tile per workgroup take
 // (before launches, outside a capture).
 hipError_t multi_prepare(int storage, int compute, int basis, int nx, int K, size_t max_lds);

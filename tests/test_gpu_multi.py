@@ -118,3 +118,25 @@ def test_an_error_has_the_same_step(flb):
             L.sync()
         assert e.value.code == flb.E_INVALID_VELOCITY
     assert a.error_step == b.error_step
+
+
+@pytest.mark.parametrize("prec,side,n", [("fp32", 32, 24), ("fp32", 32, 32), ("fp32", 32, 64),
+                                         ("fp32", 21, 80), ("fp32", 128, 4), ("fp64", 32, 16),
+                                         ("fp64", 32, 32), ("fp64", 21, 40)])
+def test_fewer_steps_as_the_chip_fills(flb, prec, side, n):
+    """Tile counts at which a launch goes from six or four steps to two and to
+    one, with the sums of every third step between the launches."""
+    ps = [flb.make_params(side, side, precision=flb.FP64 if prec == "fp64" else flb.FP32_SHIFTED,
+                          ux0=0.1, kT=1e-4, seed=k, sample_every=3 * (k % 2), block_steps=5)
+          for k in range(n)]
+    a, b = flb.Ensemble(ps), flb.Ensemble(ps)
+    b.set_launch(1, 0)
+    for steps in (13, 28):
+        a.step(steps)
+        b.step(steps)
+    for i in (0, 1, n - 1):
+        np.testing.assert_array_equal(a.populations(i), b.populations(i))
+        if i % 2:
+            ca, cb = a.covariance(i), b.covariance(i)
+            for k, v in ca.items():
+                np.testing.assert_array_equal(v, cb[k], err_msg=k)
