@@ -310,9 +310,9 @@ void flb_ensemble_destroy(flb_ensemble* E);
  * tile group its own workgroup, and they and every step computed in FP64
  * take at most 2 tiles per workgroup (a larger value is lowered to 2).
  * Two kinds of lattices and ensembles take several steps per launch where
- * the populations' memory is the library's own: small ones (up to one tile per
- * compute unit in FP32, narrow ones also in FP64), up to six steps with the
- * populations in the workgroups' LDS; and FP32 ones larger than the caches
+ * the populations' memory is the library's own: small ones (up to about one
+ * tile per compute unit in FP32, narrow ones also in FP64), up to six steps
+ * with the populations in the workgroups' LDS; and FP32 ones larger than the caches
  * (300 MiB of populations, 32 MiB in the Hermite basis), two steps per pass
  * over memory.  They write to a second population buffer, which a lattice
  * above 256 MiB takes only where seven eighths of the device's memory stay
@@ -342,7 +342,9 @@ int flb_lattice_autotune(flb_lattice* L, int32_t reps, flb_launch_config* result
                          int32_t max_results, int32_t* n_results);
 int flb_ensemble_autotune(flb_ensemble* E, int32_t reps, flb_launch_config* results,
                           int32_t max_results, int32_t* n_results);
-/* Force a shape, and one step per launch until the next autotune (FLB_E_ARG
+/* Force a shape, and one step per launch, of all replicas, until the next
+ * autotune: also the choice for several large ensembles stepped side by side
+ * on streams of their own, which overlap by themselves (FLB_E_ARG
  * for tiles_per_block not in {1, 2, 4} or a negative grid_blocks or one that
  * is not a multiple of 8). */
 int flb_lattice_set_launch(flb_lattice* L, const flb_launch_config* c);

@@ -94,8 +94,9 @@ __device__ __forceinline__ void split_bf16x3(float x, uint32_t p[3]) {
 // matrix cores; the wavefront stages its values in LDS first.
 //   FP32 storage: every df_i is split exactly into three bfloat16 parts,
 //   x = x1 + x2 + x3, so that x y = sum_{p,q} xp yq with every part product
-//   exact in FP32; eighteen v_mfma_f32_16x16x32_bf16 (the nine part pairs,
-//   32 sites each) accumulate the 16 x 16 result in FP32.  Operand layout:
+//   exact in FP32; ten v_mfma_f32_16x16x32_bf16 (32 sites each; of the part
+//   pairs p != q one product, returned transposed as well, the smallest pair
+//   left out) accumulate the 16 x 16 result in FP32.  Operand layout:
 //   lane l holds feature l % 16 of sites 8 (l / 16) .. + 7 of a group of 32
 //   (the same registers serve as A and B); result row 4 (l / 16) + r,
 //   column l % 16 in element r.  The products are exact and a wavefront's

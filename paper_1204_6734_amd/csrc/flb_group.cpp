@@ -546,9 +546,13 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
 // one branch -> two; more gained nothing): FP32 1024 tiles 5.7 -> 7.8, 2048 9.2
 // -> 8.1, 4096 (64 x 128^2) 16.2 -> 13.5, 16384 51.6 -> 46.9, 32768 101.5 ->
 // 100.1; FP64 512 tiles 5.3 -> 7.9, 1024 9.7 -> 8.4, 2048 17.8 -> 13.8, 16384
-// 116.5 -> 112.6.
+// 116.5 -> 112.6.  Several such ensembles stepped side by side on streams of
+// their own overlap by themselves, and the second branch costs there (64 x
+// 128^2 with sums every ten steps, us a step of all: one 15.4 -> 12.8, two 24.6
+// -> 26.5, three 35.9 -> 42.6): a program that does so forces a launch shape,
+// which keeps each ensemble in one branch.
 int Group::graph_branches() const {
-  if (P.size() < 2 || multi_max || d_skacc) return 1;
+  if (P.size() < 2 || multi_max || d_skacc || forced_launch) return 1;
   for (auto& h : hdesc)
     if (h.ntiles != hdesc[0].ntiles) return 1;
   return two_branches(compute, total_tiles) ? 2 : 1;

@@ -15,8 +15,7 @@
 // writes forward to its neighbours.  Each site touches the same nine
 // locations it reads, so no second buffer is needed.  The unit of work is a
 // tile of 256 sites, one wavefront per 64 consecutive sites of a row: 256 x 1
-// (four wavefronts along a row) on rows of 256 sites or more, else 64 x 4
-// (four rows).  A workgroup takes 1, 2 or 4 consecutive tiles
+// (four wavefronts along a row) or 64 x 4 (four rows), as tile_shape chooses.  A workgroup takes 1, 2 or 4 consecutive tiles
 // ("tile group"), and the grid is either one workgroup per tile group or a
 // smaller persistent grid striding over the tile groups; the autotuner picks
 // among these shapes, which all compute bit-identical results.  Tile groups

@@ -1,6 +1,6 @@
 // flb_tune.cpp — launch-shape autotuner of the batched step.
 //
-// The step kernel can run with 1, 2 or 4 tiles of 64 x 4 sites per workgroup
+// The step kernel can run with 1, 2 or 4 tiles of 256 sites per workgroup
 // and with either one workgroup per tile group or a persistent grid that
 // strides over the tile groups.  All shapes compute bit-identical results,
 // so the choice is purely a matter of speed, which depends on the device,
