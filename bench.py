@@ -44,9 +44,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_SITE = {"f32": 72, "f64": 144}
 # D3Q19 FP32 f-norm step: VALU wavefront instructions per wavefront (= per
-# site), counted in its gfx950 code and averaged over both phases,
+# site), SQ_INSTS_VALU / SQ_WAVES averaged over both phases,
 # profiles/step3_fp32_256cube_d3q19.md
-D3Q19_VALU_PER_SITE = 1950
+D3Q19_VALU_PER_SITE = 1924
 # the same of the two-step pass of the large D2Q9 FP32 lattice, per 64 site
 # updates (halo lanes and rows included), profiles/step_fp32_8192_counters.md
 MARCH_VALU_PER_SITE = 418.5
