@@ -404,7 +404,9 @@ uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
 // tiles: 3.8 -> 2.3 / 4.8 -> 3.1), and take six steps as well as four.  FP64
 // collisions gain on those only (21^2 3.7 -> 2.5 / 4.9 -> 3.5, 32^2 3.6 -> 3.1
 // / 4.9 -> 4.2; 64^2 3.7 -> 3.9 / 4.9 -> 5.5): their halo costs more than the
-// launches saved.
+// launches saved.  They take six steps with four or more rows per wavefront
+// (four -> six: 12^2 2.43 -> 2.26 / 3.23 -> 2.90, 16^2 2.45 -> 2.28; 21^2 2.51
+// -> 2.64).
 // A program may step several lattices side by side, each on its own stream,
 // and the recomputed halo then takes time from the others once they fill the
 // chip together: so the wavefronts of a launch are bounded by what three side
@@ -428,7 +430,8 @@ void Group::plan_multi(int cus) {
   const bool narrow = nx <= kTileX / 2;
   if (hdesc[0].wide || (compute == 0 && !narrow)) return;
   if (total_tiles > (narrow && compute == 1 ? 2 * cus : cus)) return;
-  const int most = narrow && compute == 1 && total_tiles <= cus ? 6 : 4;
+  const int most =
+      narrow && (compute == 1 || nx <= kTileX / 4) && total_tiles <= cus ? 6 : 4;
   for (int sample = 0; sample < 2; ++sample)
     for (int K = 2; K <= most; K += 2) {
       if (!multi_fits(storage, compute, sample != 0, nx, K, 1, max_lds)) continue;

@@ -121,7 +121,7 @@ def test_an_error_has_the_same_step(flb):
 
 
 @pytest.mark.parametrize("prec,side,n", [("fp32", 32, 24), ("fp32", 32, 32), ("fp32", 32, 64),
-                                         ("fp32", 21, 80), ("fp32", 128, 4), ("fp64", 32, 16),
+                                         ("fp32", 21, 80), ("fp32", 128, 4), ("fp64", 12, 9), ("fp64", 16, 11), ("fp64", 32, 16),
                                          ("fp64", 32, 32), ("fp64", 21, 40)])
 def test_fewer_steps_as_the_chip_fills(flb, prec, side, n):
     """Tile counts at which a launch goes from six or four steps to two and to
