@@ -246,7 +246,7 @@ struct Lattice3 {
     unsigned long long es = 0;
     HostPiece p[4] = {{&err, d_err, sizeof(err)}, {&es, d_err_step, sizeof(es)}};
     for (int i = 0; i < nmore; ++i) p[2 + i] = more[i];
-    HIPC(copy_out(p, 2 + nmore, st));
+    HIPC(copy_out(p, 2 + nmore, st, true));
     if (err) {
       err_step_host = (int64_t)es;
       if (err & kErrInvalidVelocity)

@@ -708,7 +708,7 @@ int Group::read_errors(const HostPiece* more, int nmore) {
   std::vector<HostPiece> all{{err.data(), d_err, n * sizeof(int)},
                              {es.data(), d_err_step, n * sizeof(unsigned long long)}};
   all.insert(all.end(), more, more + nmore);
-  HIPC(copy_out(all.data(), (int)all.size(), st));
+  HIPC(copy_out(all.data(), (int)all.size(), st, true));
   for (int s = 0; s < n; ++s) {
     err_step_host = -1;
     if (err[s]) {

@@ -49,7 +49,7 @@ namespace {
 // allocate (the large area costs what it saves on one readout of 14 MB), so
 // the large one is allocated by the second readout that wants it.
 constexpr size_t kSmallBytes = (size_t)256 << 10, kStageBytes = (size_t)8 << 20;
-std::mutex g_stage_count_mu, g_stage_mu;  // the count; the areas
+std::mutex g_stage_count_mu, g_small_mu, g_stage_mu;  // the count; the areas
 int g_stage_users = 0;
 bool g_stage_wanted = false;
 char *g_small = nullptr, *g_stage = nullptr;
@@ -71,7 +71,8 @@ Staging::Staging() {
 Staging::~Staging() {
   std::lock_guard<std::mutex> lk(g_stage_count_mu);
   if (--g_stage_users > 0) return;
-  std::lock_guard<std::mutex> lk2(g_stage_mu);
+  std::lock_guard<std::mutex> lk2(g_small_mu);
+  std::lock_guard<std::mutex> lk3(g_stage_mu);
   for (char** a : {&g_small, &g_stage}) {
     if (*a) (void)hipHostFree(*a);
     *a = nullptr;
@@ -79,13 +80,21 @@ Staging::~Staging() {
   g_stage_wanted = false;
 }
 
-hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st) {
-  std::unique_lock<std::mutex> lk(g_stage_mu, std::try_to_lock);
+hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st, bool behind_steps) {
   size_t total = 0;
   for (int i = 0; i < n; ++i) total += (pieces[i].bytes + 15) & ~(size_t)15;
+  const bool small = total <= kSmallBytes;
+  // the halves are polled for and hold the large area: steps enqueued before
+  // them are waited for first, asleep and without it.  A small readout waits
+  // for everything once, holding only its own area.
+  if (!small && behind_steps) {
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+  }
+  std::unique_lock<std::mutex> lk(small ? g_small_mu : g_stage_mu, std::try_to_lock);
   char* area = nullptr;
   if (lk.owns_lock()) {
-    if (total <= kSmallBytes) {
+    if (small) {
       area = locked_area(g_small, kSmallBytes);
     } else {
       if (g_stage_wanted) area = locked_area(g_stage, 2 * kStageBytes);
@@ -100,7 +109,7 @@ hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st) {
     }
     return hipStreamSynchronize(st);
   }
-  if (total <= kSmallBytes) {  // all at once, one wait
+  if (small) {  // all at once, one wait
     size_t o = 0;
     for (int i = 0; i < n; ++i) {
       const hipError_t e =

@@ -54,7 +54,8 @@ struct HostPiece {
   size_t bytes;
 };
 // Copies the pieces behind the work already enqueued on st and waits for them.
-hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st);
+// behind_steps: that work may be long (steps that nobody has waited for).
+hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st, bool behind_steps = false);
 inline hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t st) {
   const HostPiece p{dst, src, bytes};
   return copy_out(&p, 1, st);
