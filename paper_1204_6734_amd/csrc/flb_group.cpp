@@ -571,11 +571,14 @@ int Group::abandon_capture(hipError_t e) {
 int Group::capture_graph() {
   if (graph_exec) return FLB_OK;
   const int parts = graph_branches();
-  for (int i = 1; i < parts; ++i) {
-    if (!branch[i]) HIPC(hipStreamCreateWithFlags(&branch[i], hipStreamNonBlocking));
-    if (!joined[i]) HIPC(hipEventCreateWithFlags(&joined[i], hipEventDisableTiming));
+  if (parts > 1) {
+    OnDevice on(device);
+    if (!joined[0]) HIPC(hipEventCreateWithFlags(&joined[0], hipEventDisableTiming));
+    for (int i = 1; i < parts; ++i) {
+      if (!branch[i]) HIPC(hipStreamCreateWithFlags(&branch[i], hipStreamNonBlocking));
+      if (!joined[i]) HIPC(hipEventCreateWithFlags(&joined[i], hipEventDisableTiming));
+    }
   }
-  if (!joined[0]) HIPC(hipEventCreateWithFlags(&joined[0], hipEventDisableTiming));
   HIPC(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   if (parts > 1) {
     hipError_t e = hipEventRecord(joined[0], st);

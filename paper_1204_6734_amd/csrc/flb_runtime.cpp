@@ -131,8 +131,13 @@ hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st, bool behind_
   }
   // in halves: one is copied on to the caller while the other fills
   hipEvent_t ev[2] = {nullptr, nullptr};
-  hipError_t e = hipEventCreateWithFlags(&ev[0], hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[1], hipEventDisableTiming);
+  hipDevice_t device = 0;
+  hipError_t e = hipStreamGetDevice(st, &device);
+  if (e == hipSuccess) {
+    OnDevice on(device);
+    e = hipEventCreateWithFlags(&ev[0], hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[1], hipEventDisableTiming);
+  }
   char* dst[2] = {nullptr, nullptr};
   size_t len[2] = {0, 0};
   int h = 0;

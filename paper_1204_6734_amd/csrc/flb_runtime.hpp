@@ -35,6 +35,25 @@ void hermite_rows(double m[81]);
 double equilibrium(int i, double rho, double ux, double uy);
 bool fnorm_rows(double ux, double uy, double mt[81]);
 
+// Makes a device the calling thread's current one while it lives: events and
+// streams belong to the device they are created on, and a thread may use a
+// lattice of another device than its current one.
+class OnDevice {
+ public:
+  explicit OnDevice(int device) {
+    if (hipGetDevice(&was_) != hipSuccess || was_ == device) was_ = -1;
+    else if (hipSetDevice(device) != hipSuccess) was_ = -1;
+  }
+  ~OnDevice() {
+    if (was_ >= 0) (void)hipSetDevice(was_);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+
+ private:
+  int was_ = -1;
+};
+
 // Readouts to caller-owned host memory go through page-locked staging: a copy
 // of 14 MB straight into pageable memory takes 0.86 ms, through it 0.45, and
 // every small piece 10 to 15 us.  The staging is the process's, held while any

@@ -62,3 +62,25 @@ for L in (F.Lattice(P(16, 16, sample_every=1, block_steps=1)),
         waits = [int(x.split()[2]) for x in lines if x[0] == "S"]
         assert waits[0] > 0, lines
 """)
+
+
+@pytest.mark.parametrize("case", ["readout", "graph"])
+def test_another_current_device(program, case):
+    """A lattice or ensemble of device 0 used while device 1 is current, as
+    programs that hold lattices on several devices do: large readouts, and the
+    replayed chunk of an ensemble that advances in two halves."""
+    program("""
+if %r == "readout":
+    L = F.Lattice(P(200, 200))
+    fake.hipSetDevice(1)
+    for _ in range(3):
+        L.populations()
+else:
+    L = F.Ensemble([P(128, 128, seed=k) for k in range(64)], graph_chunk=10)
+    fake.hipSetDevice(1)
+    L.step(20)
+    assert len({x.split()[1] for x in log("C", "step_kernel")}) == 2
+now = C.c_int()
+fake.hipGetDevice(C.byref(now))
+assert now.value == 1
+""" % case)
