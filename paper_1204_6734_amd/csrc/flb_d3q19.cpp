@@ -56,7 +56,8 @@ struct Lattice3 {
   flb3_params p{};
   int storage = 1;
   size_t N = 0;
-  int cus = 256;
+  int cus = 256, device = 0;
+  AtWork at_work;
   Desc3 h{};
   Desc3* d_desc = nullptr;
   char* dev = nullptr;
@@ -157,9 +158,8 @@ struct Lattice3 {
     d_open = (double*)q;
     h.err = d_err;
     h.err_step = d_err_step;
-    int dev_id = 0;
-    HIPC(hipGetDevice(&dev_id));
-    HIPC(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id));
+    HIPC(hipGetDevice(&device));
+    HIPC(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
     if (stream) {
       st = (hipStream_t)stream;
     } else {
@@ -204,6 +204,7 @@ struct Lattice3 {
 
   int step(uint64_t n) {
     const uint64_t chunk_max = 1ull << 30;
+    if (n) at_work.begin(device);
     uint64_t done = 0;
     while (done < n) {
       const uint64_t chunk = std::min(n - done, chunk_max);
@@ -246,7 +247,8 @@ struct Lattice3 {
     unsigned long long es = 0;
     HostPiece p[4] = {{&err, d_err, sizeof(err)}, {&es, d_err_step, sizeof(es)}};
     for (int i = 0; i < nmore; ++i) p[2 + i] = more[i];
-    HIPC(copy_out(p, 2 + nmore, st, true));
+    HIPC(copy_out(p, 2 + nmore, st, at_work.begun()));
+    at_work.end();
     if (err) {
       err_step_host = (int64_t)es;
       if (err & kErrInvalidVelocity)
@@ -326,6 +328,7 @@ struct Lattice3 {
 
   int reset_stats() {
     HIPC(hipStreamSynchronize(st));
+    at_work.end();
     if (h.partials) HIPC(launch_fill3(h.partials, (size_t)h.ntiles * kNStat3, st));
     reset_blocks();
     return FLB_OK;
@@ -333,6 +336,7 @@ struct Lattice3 {
 
   int kernel_time(double* ms, uint64_t* launches) {
     HIPC(hipStreamSynchronize(st));
+    at_work.end();
     double tot = 0;
     for (auto& e : events) {
       float m = 0;
@@ -380,6 +384,7 @@ int flb3_lattice_set_populations(flb3_lattice* L, const double* f, uint64_t t) {
   if (!f) return flb::set_error(FLB_E_ARG, "null populations");
   hipError_t e = hipStreamSynchronize(L->L.st);
   if (e != hipSuccess) return flb::hip_fail(e, "sync");
+  L->L.at_work.end();
   L->L.t = t;
   e = hipMemcpy(L->L.d_clock, &t, sizeof(uint64_t), hipMemcpyHostToDevice);
   if (e != hipSuccess) return flb::hip_fail(e, "clock");

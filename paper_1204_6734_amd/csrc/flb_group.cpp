@@ -256,13 +256,12 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
 }
 
 Group::~Group() {
-  if (st) (void)hipStreamSynchronize(st);
+  if (st) (void)wait();
   for (auto& e : events) {
     (void)hipEventDestroy(e.first);
     (void)hipEventDestroy(e.second);
   }
-  if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-  if (graph) (void)hipGraphDestroy(graph);
+  drop_graph();
   for (int i = 0; i < kMaxBranches; ++i) {
     if (joined[i]) (void)hipEventDestroy(joined[i]);
     if (branch[i]) (void)hipStreamDestroy(branch[i]);
@@ -549,16 +548,27 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
 // one branch -> two; more gained nothing): FP32 1024 tiles 5.7 -> 7.8, 2048 9.2
 // -> 8.1, 4096 (64 x 128^2) 16.2 -> 13.5, 16384 51.6 -> 46.9, 32768 101.5 ->
 // 100.1; FP64 512 tiles 5.3 -> 7.9, 1024 9.7 -> 8.4, 2048 17.8 -> 13.8, 16384
-// 116.5 -> 112.6.  Several such ensembles stepped side by side on streams of
-// their own overlap by themselves, and the second branch costs there (64 x
-// 128^2 with sums every ten steps, us a step of all: one 15.4 -> 12.8, two 24.6
-// -> 26.5, three 35.9 -> 42.6): a program that does so forces a launch shape,
-// which keeps each ensemble in one branch.
-int Group::graph_branches() const {
+// 116.5 -> 112.6.  Ensembles stepped side by side on streams of their own fill
+// the chip by themselves, and the second branch costs there until their
+// populations outgrow the last-level cache; so beside other work it is taken
+// from 16384 tiles on (FP64 8192).  us a step of all, one branch -> two:
+//                two at once                three at once
+//   FP32  2048   12.2 -> 15.2               18.8 -> 22.9
+//         4096   23.7 -> 27.4               34.9 -> 42.0
+//         8192   45.0 -> 48.4               66.9 -> 77.1
+//        12288   67.0 -> 70.7, with sums    115.6 -> 109.7, with sums
+//                76.4 -> 73.0               117.1 -> 112.4
+//        16384   98.0 -> 89.3               158.8 -> 137.5
+//   FP64  1024   14.1 -> 16.7               20.3 -> 25.0
+//         4096   51.4 -> 53.2               76.5 -> 84.8
+//         8192   112.2 -> 103.7             171.6 -> 160.3
+// Alone means at this replay and the one before: of ensembles stepped in turn
+// and then waited for, the first to go on is not taken for a lone one.
+int Group::graph_branches(bool alone) const {
   if (P.size() < 2 || multi_max || d_skacc || forced_launch) return 1;
   for (auto& h : hdesc)
     if (h.ntiles != hdesc[0].ntiles) return 1;
-  return two_branches(compute, total_tiles) ? 2 : 1;
+  return two_branches(compute, total_tiles, alone) ? 2 : 1;
 }
 
 int Group::abandon_capture(hipError_t e) {
@@ -568,9 +578,8 @@ int Group::abandon_capture(hipError_t e) {
   return hip_fail(e, "capture step");
 }
 
-int Group::capture_graph() {
-  if (graph_exec) return FLB_OK;
-  const int parts = graph_branches();
+int Group::capture_graph(int parts) {
+  if (graph_exec[parts - 1]) return FLB_OK;
   if (parts > 1) {
     OnDevice on(device);
     if (!joined[0]) HIPC(hipEventCreateWithFlags(&joined[0], hipEventDisableTiming));
@@ -624,8 +633,8 @@ int Group::capture_graph() {
     if (e != hipSuccess) return abandon_capture(e);
   }
   HIPC(launch_tick(d_clock, (uint64_t)graph_chunk, st));
-  HIPC(hipStreamEndCapture(st, &graph));
-  HIPC(hipGraphInstantiate(&graph_exec, graph, nullptr, nullptr, 0));
+  HIPC(hipStreamEndCapture(st, &graph[parts - 1]));
+  HIPC(hipGraphInstantiate(&graph_exec[parts - 1], graph[parts - 1], nullptr, nullptr, 0));
   return FLB_OK;
 }
 
@@ -634,22 +643,27 @@ int Group::step(uint64_t nsteps) {
   const uint64_t K = (uint64_t)graph_chunk;
   const bool use_graph = graph_friendly();
   uint64_t done = 0;
+  if (nsteps) at_work.begin(device);
   while (done < nsteps) {
     const uint64_t left = nsteps - done;
     if (use_graph && left >= K && t % K == 0 && steps_to_close(t, 0) >= K) {
-      int rc = capture_graph();
+      const bool others = at_work.others(device);
+      const int parts = graph_branches(!others && !shared);
+      shared = others;
+      int rc = capture_graph(parts);
       if (rc != FLB_OK) return rc;
+      hipGraphExec_t exec = graph_exec[parts - 1];
       if (profiling) {
         std::pair<hipEvent_t, hipEvent_t> ev;
         HIPC(hipEventCreate(&ev.first));
         HIPC(hipEventCreate(&ev.second));
         HIPC(hipEventRecord(ev.first, st));
-        HIPC(hipGraphLaunch(graph_exec, st));
+        HIPC(hipGraphLaunch(exec, st));
         HIPC(hipEventRecord(ev.second, st));
         events.push_back(ev);
         prof_launches += K;
       } else {
-        HIPC(hipGraphLaunch(graph_exec, st));
+        HIPC(hipGraphLaunch(exec, st));
       }
       for (uint64_t k = 0; k < K; ++k) {
         rc = after_step(t + k, true);
@@ -697,6 +711,12 @@ int Group::step(uint64_t nsteps) {
   return FLB_OK;
 }
 
+hipError_t Group::wait() {
+  const hipError_t e = hipStreamSynchronize(st);
+  at_work.end();
+  return e;
+}
+
 int Group::sync() {
   // waits for the stream too
   return read_errors(nullptr, 0);
@@ -711,7 +731,8 @@ int Group::read_errors(const HostPiece* more, int nmore) {
   std::vector<HostPiece> all{{err.data(), d_err, n * sizeof(int)},
                              {es.data(), d_err_step, n * sizeof(unsigned long long)}};
   all.insert(all.end(), more, more + nmore);
-  HIPC(copy_out(all.data(), (int)all.size(), st, true));
+  HIPC(copy_out(all.data(), (int)all.size(), st, at_work.begun()));
+  at_work.end();
   for (int s = 0; s < n; ++s) {
     err_step_host = -1;
     if (err[s]) {
@@ -781,7 +802,7 @@ int Group::read_rows(int s, int y0, int nrows, double* f) {
 }
 
 int Group::set_populations(int s, const double* f, uint64_t tnew) {
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   const flb_params& p = P[s];
   const size_t N = (size_t)p.nx * p.ny;
   if (P.size() != 1) return set_error(FLB_E_STATE, "set_populations needs a single lattice");
@@ -793,13 +814,13 @@ int Group::set_populations(int s, const double* f, uint64_t tnew) {
     if (rc != FLB_OK) return rc;
     HIPC(launch_write_state(storage, pop[s], hdesc[s].pitch, d_io, p.nx, p.ny, (int)(t & 1), slot_shift(hdesc[s]),
                             y0, rows, st));
-    HIPC(hipStreamSynchronize(st));
+    HIPC(wait());
   }
   return FLB_OK;
 }
 
 int Group::set_fields(int s, const double* rho, const double* ux, const double* uy) {
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   const flb_params& p = P[s];
   for (int y0 = 0; y0 < p.ny; y0 += band_rows) {
     const int rows = std::min(band_rows, p.ny - y0);
@@ -810,7 +831,7 @@ int Group::set_fields(int s, const double* rho, const double* ux, const double* 
     HIPC(launch_init(storage, pop[s], hdesc[s].pitch, d_io, d_io + B, d_io + 2 * B, p.rho0, p.ux0, p.uy0,
                      slot_shift(hdesc[s]), p.nx, p.ny, 0.0, hdesc[s].k0, hdesc[s].k1,
                      (int)(t & 1), y0, rows, st));
-    HIPC(hipStreamSynchronize(st));
+    HIPC(wait());
   }
   return FLB_OK;
 }
@@ -826,7 +847,7 @@ int Group::read_moments(int s, int at, double* m) {
     if (at == FLB_AT_U0) std::memcpy(h, mt0[s].data(), sizeof(h));
     else hermite_rows(h);
     HIPC(hipMemcpyAsync(d_B, h, sizeof(h), hipMemcpyHostToDevice, st));
-    HIPC(hipStreamSynchronize(st));
+    HIPC(wait());
     B = d_B;
   } else if (at != FLB_AT_LOCAL) {
     return set_error(FLB_E_ARG, "unknown moment basis %d", at);
@@ -860,7 +881,7 @@ int Group::read_covariance(int s, flb_cov* out) {
 }
 
 int Group::reset_stats() {
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   for (int s = 0; s < (int)P.size(); ++s) {
     stats[s].reset(P[s].block_steps);
     if (d_partials[s]) {
@@ -870,7 +891,7 @@ int Group::reset_stats() {
   }
   if (d_skacc) HIPC(launch_fill(d_skacc, 5 * sk_half(), 0.0, st));
   nsk = 0;
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   return FLB_OK;
 }
 
@@ -949,7 +970,7 @@ int Group::checkpoint(void* host, size_t bytes) {
 }
 
 int Group::restore(const void* host, size_t bytes) {
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   if (bytes < sizeof(CkptHeader)) return set_error(FLB_E_ARG, "checkpoint too short");
   CkptHeader h;
   std::memcpy(&h, host, sizeof(h));
@@ -970,13 +991,13 @@ int Group::restore(const void* host, size_t bytes) {
     const int rc = copy_planes_in(src, N, (size_t)y0 * p.nx, (size_t)rows * p.nx, es);
     if (rc != FLB_OK) return rc;
     HIPC(launch_raw_state(storage, pop[0], hdesc[0].pitch, d_io, p.nx, p.ny, (int)(t & 1), 0, y0, rows, st));
-    HIPC(hipStreamSynchronize(st));
+    HIPC(wait());
   }
   return reset_stats();
 }
 
 int Group::kernel_time(double* ms, uint64_t* launches) {
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   double tot = 0;
   for (auto& e : events) {
     float m = 0;
@@ -1063,7 +1084,7 @@ int flb_lattice_set_populations(flb_lattice* L, const double* f, uint64_t t) {
 int flb_lattice_set_graph_chunk(flb_lattice* L, int32_t steps) {
   NEED(L);
   if (steps < 0 || steps > (1 << 16)) return flb::set_error(FLB_E_ARG, "bad chunk %d", steps);
-  const hipError_t e = hipStreamSynchronize(L->g.st);  // no replay in flight
+  const hipError_t e = L->g.wait();  // no replay in flight
   if (e != hipSuccess) return flb::hip_fail(e, "sync");
   L->g.drop_graph();
   L->g.graph_chunk = steps + (steps & 1);  // even: replays keep the streaming phase
@@ -1126,7 +1147,7 @@ int flb_lattice_restore(flb_lattice* L, const void* host, size_t bytes) {
 int flb_lattice_population_buffer(flb_lattice* L, void** dev, size_t* bytes, uint64_t* t) {
   NEED(L);
   if (!dev || !bytes || !t) return flb::set_error(FLB_E_ARG, "null output");
-  const hipError_t e = hipStreamSynchronize(L->g.st);
+  const hipError_t e = L->g.wait();
   if (e != hipSuccess) return flb::hip_fail(e, "sync");
   const flb_params& p = L->g.P[0];
   *dev = L->g.pop[0];
@@ -1163,7 +1184,7 @@ int flb_ensemble_create(const flb_params* ps, int32_t n, void* hip_stream, flb_e
 int flb_ensemble_set_graph_chunk(flb_ensemble* E, int32_t steps) {
   NEED(E);
   if (steps < 0 || steps > (1 << 16)) return flb::set_error(FLB_E_ARG, "bad chunk %d", steps);
-  const hipError_t e = hipStreamSynchronize(E->g.st);  // no replay in flight
+  const hipError_t e = E->g.wait();  // no replay in flight
   if (e != hipSuccess) return flb::hip_fail(e, "sync");
   E->g.drop_graph();
   E->g.graph_chunk = steps + (steps & 1);  // even: replays keep the streaming phase

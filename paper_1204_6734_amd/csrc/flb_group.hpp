@@ -75,13 +75,16 @@ struct Group {
   // rows a wavefront of the two-step pass over a large lattice takes (0: the
   // launches of several steps are those of small lattices)
   int march_rows = 0;
-  // graphs
+  // graphs: the captured chunk in one branch and in two, each captured when
+  // it is first replayed (graph_branches)
   int graph_chunk = 0;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
+  static constexpr int kMaxBranches = 2;
+  hipGraph_t graph[kMaxBranches] = {nullptr};
+  hipGraphExec_t graph_exec[kMaxBranches] = {nullptr};
+  AtWork at_work;
+  bool shared = false;  // something else was at work at the last replay
   // side branches of the captured graph: their streams (from 1) and the
   // events that fork (0) and join them
-  static constexpr int kMaxBranches = 2;
   hipStream_t branch[kMaxBranches] = {nullptr};
   hipEvent_t joined[kMaxBranches] = {nullptr};
   // profiling
@@ -106,7 +109,7 @@ struct Group {
   hipError_t launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c);
   hipError_t launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c, int part, int parts,
                             hipStream_t q);
-  int graph_branches() const;
+  int graph_branches(bool alone) const;
   bool graph_friendly() const;
   uint64_t steps_to_close(uint64_t tt, uint64_t skip) const;
   int abandon_capture(hipError_t e);
@@ -117,8 +120,9 @@ struct Group {
   bool pass_samples(uint64_t tt, int K) const;
   void pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb) const;
   hipError_t launch_pass(uint32_t k, uint64_t tt, int K, int flip);
-  int capture_graph();
+  int capture_graph(int parts);
   int step(uint64_t nsteps);
+  hipError_t wait();
   int sync();
   int read_errors(const HostPiece* more, int nmore);
   int copy_planes(void* dst, size_t N, size_t off, size_t B, size_t es);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -41,6 +42,29 @@ int hip_fail(hipError_t e, const char* what) {
     hipError_t e_ = (expr);                          \
     if (e_ != hipSuccess) return hip_fail(e_, #expr); \
   } while (0)
+
+// ---------------------------------------------------------------- at work
+namespace {
+constexpr int kMaxDevices = 64;  // above: never anything else at work
+std::atomic<int> g_at_work[kMaxDevices];
+}  // namespace
+
+void AtWork::begin(int device) {
+  if (on_ >= 0 || device < 0 || device >= kMaxDevices) return;
+  on_ = device;
+  g_at_work[device].fetch_add(1, std::memory_order_relaxed);
+}
+
+void AtWork::end() {
+  if (on_ < 0) return;
+  g_at_work[on_].fetch_sub(1, std::memory_order_relaxed);
+  on_ = -1;
+}
+
+bool AtWork::others(int device) const {
+  if (device < 0 || device >= kMaxDevices) return false;
+  return g_at_work[device].load(std::memory_order_relaxed) > (on_ == device ? 1 : 0);
+}
 
 // ---------------------------------------------------------------- readouts
 namespace {

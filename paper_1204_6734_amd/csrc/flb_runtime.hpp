@@ -23,8 +23,12 @@ int hip_fail(hipError_t e, const char* what);
 int check_params(const flb_params* p);
 int compute_precision(const flb_params* p);
 // Whether this many tiles of independent lattices are stepped faster as two
-// halves side by side (compute: 0 FP64, 1 FP32).
-inline bool two_branches(int compute, int tiles) { return tiles >= (compute == 0 ? 1024 : 2048); }
+// halves side by side (compute: 0 FP64, 1 FP32; the measurements are beside
+// Group::graph_branches), alone on the device or beside other work.
+inline bool two_branches(int compute, int tiles, bool alone) {
+  const int least = alone ? 1024 : 8192;
+  return tiles >= (compute == 0 ? least : 2 * least);
+}
 uint32_t row_pitch(int nx);
 size_t population_elems(int nx, int ny);
 void tile_shape(const flb_params& p, int* wide, int* tiles_x, int* ntiles);
@@ -52,6 +56,26 @@ class OnDevice {
 
  private:
   int was_ = -1;
+};
+
+// Whether a lattice, ensemble or server has work enqueued that the library has
+// not waited for since, counted over the process by device: launches that pay
+// only while nothing else fills the chip ask for others().  A program that
+// waits by its own means (its stream's, the device's synchronisation) is taken
+// to be at work until its next readout or sync.
+class AtWork {
+ public:
+  AtWork() = default;
+  ~AtWork() { end(); }
+  AtWork(const AtWork&) = delete;
+  AtWork& operator=(const AtWork&) = delete;
+  void begin(int device);
+  void end();
+  bool begun() const { return on_ >= 0; }
+  bool others(int device) const;
+
+ private:
+  int on_ = -1;  // the device, while at work
 };
 
 // Readouts to caller-owned host memory go through page-locked staging: a copy

@@ -138,6 +138,8 @@ struct flb_server {
   // fork and join it
   hipStream_t st2 = nullptr;
   hipEvent_t forked = nullptr, joined = nullptr;
+  int device = 0;
+  AtWork at_work;
   std::chrono::steady_clock::time_point t_start;
   double busy = 0;
   std::thread worker;
@@ -265,6 +267,7 @@ int flb_server::finish(const Active& a) {
 // failure the requests not yet retired stay in it.
 int flb_server::retire() {
   HIPC(hipStreamSynchronize(st));
+  at_work.end();
   std::vector<Active> keep;
   int rc = FLB_OK;
   for (const Active& a : active) {
@@ -293,6 +296,8 @@ int flb_server::run_chunk() {
   std::vector<Half> halves;
   std::vector<hipStream_t> stream_of(active.size(), st);
   bool two = false;
+  at_work.begin(device);
+  const bool alone = !at_work.others(device);
   for (int c = 0; c < 2; ++c) {
     h_slots[c].clear();
     h_prefix[c].clear();
@@ -303,7 +308,7 @@ int flb_server::run_chunk() {
         ++n;
       }
     if (!n) continue;
-    const bool split = n > 1 && two_branches(c, total);
+    const bool split = n > 1 && two_branches(c, total, alone);
     // in order, each request to the lighter half
     int load[2] = {0, 0};
     std::vector<int> half(active.size(), 0);
@@ -441,7 +446,8 @@ int flb_server_create(const flb_server_config* cfg, void* hip_stream, flb_server
     flb_server_destroy(S);
     return rc;
   };
-  hipError_t e;
+  hipError_t e = hipGetDevice(&S->device);
+  if (e != hipSuccess) return fail(hip_fail(e, "device"));
   if (hip_stream) {
     S->st = (hipStream_t)hip_stream;
   } else {

@@ -71,17 +71,19 @@ LaunchCfg tuned_launch(const Group& g) {
 }
 
 void Group::drop_graph() {
-  if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-  if (graph) (void)hipGraphDestroy(graph);
-  graph_exec = nullptr;
-  graph = nullptr;
+  for (int i = 0; i < kMaxBranches; ++i) {
+    if (graph_exec[i]) (void)hipGraphExecDestroy(graph_exec[i]);
+    if (graph[i]) (void)hipGraphDestroy(graph[i]);
+    graph_exec[i] = nullptr;
+    graph[i] = nullptr;
+  }
 }
 
 int Group::set_launch(const flb_launch_config* c) {
   if (!c || !valid(*c))
     return set_error(FLB_E_ARG, "launch shape: tiles_per_block must be 1, 2 or 4 and "
                                 "grid_blocks a non-negative multiple of 8");
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   drop_graph();
   launch = LaunchCfg{c->tiles_per_block, c->grid_blocks};
   forced_launch = true;
@@ -93,7 +95,7 @@ int Group::autotune(int reps, flb_launch_config* results, int max_results, int* 
   if (max_results < 0 || (max_results > 0 && !results))
     return set_error(FLB_E_ARG, "null results array");
   const int n = (int)P.size();
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   int cus = 0;
   HIPC(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
   // snapshot of everything a trial step writes: populations and error flags
@@ -190,7 +192,7 @@ int Group::autotune(int reps, flb_launch_config* results, int max_results, int* 
   const hipError_t back = copy(false);
   if (tr != hipSuccess) return hip_fail(tr, "autotune trial steps");
   if (back != hipSuccess) return hip_fail(back, "autotune: restoring the populations");
-  HIPC(hipStreamSynchronize(st));
+  HIPC(wait());
   std::stable_sort(meas.begin(), meas.end(),
                    [](const flb_launch_config& a, const flb_launch_config& b) {
                      return a.ms_per_step < b.ms_per_step;

@@ -4,7 +4,7 @@
 // memory, kernels are log lines, and work is finished by waiting for it.
 //
 // Log, one line each: K <stream> <kernel> (a launch), C ... (the same, into a
-// captured graph), G <stream> (a replay), M <bytes> (an allocation), S <stream>
+// captured graph), G <stream> <branches> (a replay), M <bytes> (an allocation), S <stream>
 // <steps> (a wait for a stream with that many step launches pending), P <stream>
 // (an event asked for while step launches recorded before it are pending).
 #include <hip/hip_runtime.h>
@@ -14,6 +14,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 
 namespace {
@@ -37,6 +38,10 @@ std::string fail_name;
 hipError_t last = hipSuccess;
 thread_local int current = 0;
 Stream null_stream{0, 0};
+std::set<Stream*> captured;  // streams with launches in the current capture
+struct Graph {
+  size_t branches;
+};
 
 Stream* of(hipStream_t s) { return s ? (Stream*)s : &null_stream; }
 void put(const std::string& s) { text += s + "\n"; }
@@ -93,6 +98,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t lds, hi
   if (fail_in > 0 && n.find(fail_name) != std::string::npos && --fail_in == 0)
     return error(hipErrorLaunchFailure);
   put((s->capturing ? "C " : "K ") + std::to_string(s->id) + " " + n);
+  if (s->capturing) captured.insert(s);
   if (!s->capturing && n.find("step") != std::string::npos) ++s->steps;
   return hipSuccess;
 }
@@ -173,24 +179,25 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   return hipSuccess;
 }
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
+  captured.clear();
   return of(s)->capturing = true, hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
   Lock lk(mu);
   for (auto& s : streams) s.first->capturing = false;
-  return *g = (hipGraph_t) new int, hipSuccess;
+  return *g = (hipGraph_t) new Graph{captured.size()}, hipSuccess;
 }
-hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t, hipGraphNode_t*, char*, size_t) {
-  return *x = (hipGraphExec_t) new int, hipSuccess;
+hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*, char*, size_t) {
+  return *x = (hipGraphExec_t) new Graph(*(Graph*)g), hipSuccess;
 }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) {
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s) {
   Lock lk(mu);
-  put("G " + std::to_string(of(s)->id));
+  put("G " + std::to_string(of(s)->id) + " " + std::to_string(((Graph*)x)->branches));
   ++of(s)->steps;
   return hipSuccess;
 }
-hipError_t hipGraphDestroy(hipGraph_t g) { return delete (int*)g, hipSuccess; }
-hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return delete (int*)x, hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t g) { return delete (Graph*)g, hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t x) { return delete (Graph*)x, hipSuccess; }
 
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
   return *e = (hipEvent_t) new Event{current}, hipSuccess;

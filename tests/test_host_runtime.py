@@ -84,3 +84,80 @@ now = C.c_int()
 fake.hipGetDevice(C.byref(now))
 assert now.value == 1
 """ % case)
+
+
+@pytest.mark.parametrize("other", ["ensemble", "lattice", "d3q19", "server"])
+def test_two_graph_branches_only_while_nothing_else_is_at_work(program, other):
+    """An ensemble that fills the chip replays two branches alone, one while
+    another object has work that was not waited for, and two again after."""
+    program("""
+def ensemble():
+    return F.Ensemble([P(128, 128, seed=k, sample_every=5) for k in range(64)], graph_chunk=10)
+
+class Server:  # at work between a failed chunk and its end
+    def __init__(self):
+        self.S = F.Server(1 << 28, threaded=False, chunk_steps=4)
+        self.S.submit(P(64, 64), 8)
+    def step(self, n):
+        fake.fake_fail(b"step_kernel", 3)
+        try:
+            self.S.pump(1)
+            raise SystemExit("no failure")
+        except F.FlbError:
+            pass
+    def sync(self):
+        self.S.pump(1)
+
+E = ensemble()
+O = {"ensemble": ensemble, "lattice": lambda: F.Lattice(P(64, 64)), "server": Server,
+     "d3q19": lambda: F.Lattice3(F.make_params3(8, 8, 8))}[%r]()
+
+def branches():
+    log()
+    E.step(20)
+    return [int(x.split()[2]) for x in log("G")]
+
+assert branches() == [2, 2]
+O.step(10)
+if %r == "ensemble":
+    assert [x.split()[2] for x in log("G")] == ["1"]  # E is still at work
+assert branches() == [1, 1]
+O.sync()
+assert branches() == [1, 2] and not log("C")  # alone at two replays
+O.step(10)
+del O
+assert branches() == [2, 2]
+""" % (other, other))
+
+
+@pytest.mark.parametrize("prec,n,branches", [("FP32_SHIFTED", 255, 1), ("FP32_SHIFTED", 256, 2),
+                                             ("FP64", 127, 1), ("FP64", 128, 2)])
+def test_populations_beyond_the_cache_take_two_branches_beside_other_work(program, prec, n,
+                                                                          branches):
+    program("""
+E = F.Ensemble([P(128, 128, seed=k, precision=F.%s) for k in range(%d)], graph_chunk=10)
+L = F.Lattice(P(64, 64))
+L.step(10)
+E.step(10)
+assert [x.split()[2] for x in log("G")] == ["%d"]
+""" % (prec, n, branches))
+
+
+def test_a_server_takes_two_streams_only_alone(program):
+    program("""
+S = F.Server(1 << 30, threaded=False, chunk_steps=4)
+for k in range(40):
+    S.submit(P(128, 128, seed=k), 12)
+L = F.Lattice(P(64, 64))
+
+def streams():
+    log()
+    S.pump(1)
+    return len({x.split()[1] for x in log("K", "step_kernel")})
+
+assert streams() == 2
+L.step(1)
+assert streams() == 1
+L.sync()
+assert streams() == 2
+""")
