@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <numeric>
 #include <vector>
 
 #include "flb.h"
@@ -107,7 +108,12 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
   }
   hdesc.assign(n, SlotDesc{});
   prefix.assign(n + 1, 0);
+  sample_intervals.clear();
   for (int s = 0; s < n; ++s) {
+    const uint64_t every = (uint64_t)ps[s].sample_every;
+    if (every && std::find(sample_intervals.begin(), sample_intervals.end(), every) ==
+                     sample_intervals.end())
+      sample_intervals.push_back(every);
     fill_slot(&ps[s], &hdesc[s]);
     prefix[s + 1] = prefix[s] + hdesc[s].ntiles;
   }
@@ -130,6 +136,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
   } else {
     hipError_t e = hipErrorOutOfMemory;
     plan_multi(cus);
+    if (!passes_pay()) multi_max = march_rows = 0;
     if (multi_max) {
       Arena both;
       layout(both, true);
@@ -169,7 +176,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
                      (int)(max_lds / sizeof(double2)), (int)(max_lds / sizeof(float2)),
                      kMaxDirectDft);
   if (multi_max && !march_rows)
-    for (int c = 0; c < nclass; ++c) 
+    for (int c = 0; c < nclass; ++c)
       HIPC(multi_prepare(storage, ccompute[c], basis, P[0].nx, multi_max, max_lds));
   launch = tuned_launch(*this);
   // per-slot pointers and measurement bases
@@ -492,9 +499,7 @@ bool Group::take_second(size_t bytes) const {
 // Largest launch from the even time tt within `lim` steps that holds no
 // structure-factor step but its first.
 int Group::pass_steps(uint64_t tt, uint64_t lim) const {
-  for (int s = 0; s < (int)P.size(); ++s)
-    if (d_skacc && P[s].sk_every > 0)
-      lim = std::min(lim, (uint64_t)P[s].sk_every - tt % (uint64_t)P[s].sk_every);
+  if (const uint64_t sk = (uint64_t)sk_interval()) lim = std::min(lim, sk - tt % sk);
   for (int K = multi_max; K >= 2; K -= 2)
     if ((uint64_t)K <= lim && multi_nt[pass_samples(tt, K)][K]) return K;
   return 0;
@@ -502,10 +507,10 @@ int Group::pass_steps(uint64_t tt, uint64_t lim) const {
 
 // Whether a launch of K steps from time tt takes the variant with sums.
 bool Group::pass_samples(uint64_t tt, int K) const {
-  for (int s = 0; s < (int)P.size(); ++s) {
-    const uint64_t se = (uint64_t)P[s].sample_every;
-    if (sk_due(s, tt) || (se > 0 && (tt + se - 1) / se * se < tt + (uint64_t)K)) return true;
-  }
+  const uint64_t sk = (uint64_t)sk_interval();
+  if (sk && tt % sk == 0) return true;
+  for (uint64_t se : sample_intervals)
+    if ((tt + se - 1) / se * se < tt + (uint64_t)K) return true;
   return false;
 }
 
@@ -523,6 +528,47 @@ void Group::pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb)
     *kb = pass_steps(tt + (uint64_t)K, std::min(left - (uint64_t)K, m2));
     if (*kb) return;
   }
+}
+
+// Share of the first `steps` steps (0: of some periods of the sampling) that
+// launches of several steps take, time blocks aside.
+double Group::pass_share(uint64_t steps) const {
+  if (!multi_max) return 0.0;
+  if (!steps) {
+    uint64_t period = 2;
+    for (uint64_t e : sample_intervals) period = std::min<uint64_t>(std::lcm(period, e), 2048);
+    if (const uint64_t sk = (uint64_t)sk_interval())
+      period = std::min<uint64_t>(std::lcm(period, sk), 2048);
+    steps = (96 + period - 1) / period * period;
+  }
+  uint64_t taken = 0;
+  for (uint64_t tt = 0; tt < steps;) {
+    int pass[2];
+    pass_pair(tt, steps - tt, false, &pass[0], &pass[1]);
+    const uint64_t k = pass[1] ? (uint64_t)(pass[0] + pass[1]) : 0;
+    taken += k;
+    tt += k ? k : 1;
+  }
+  return (double)taken / (double)steps;
+}
+
+// Whether what was planned pays with the members' sampling.  Where only steps
+// without sums are taken together, a lattice that samples every step has none
+// and needs no second buffer.  In the f-norm bases, strips that use less than
+// nine tenths of their lanes lose in part of the steps more than they gain in
+// the others below 400 MiB, and beyond with few such steps (us a step, one step
+// per launch -> passes; sums every 5, 8, 10, no steps: 160 x 256^2, 360 MiB,
+// 139.0 -> 143.7, 137.1 -> 141.6, 136.7 -> 138.1, 134.0 -> 133.2; 200 x 256^2, 450
+// MiB, 175.6 -> 178.8, 173.8 -> 176.0, 173.3 -> 170.3, 170.7 -> 164.2).  Wider strips gain throughout (8192^2 873 -> 837, 859
+// -> 818, 856 -> 764; 3072^2 121 -> 119, 119 -> 117, 119 -> 113), and so does the
+// Hermite basis (64 x 160^2 20.3 -> 18.7, 20.2 -> 18.1, 20.1 -> 16.6).
+bool Group::passes_pay() const {
+  const double share = pass_share();
+  if (!march_rows || basis == FLB_BASIS_HERMITE) return share > 0;
+  const int nx = P[0].nx, strips = (nx + kMarchCols - 1) / kMarchCols;
+  const double bytes = (double)population_elems(nx, P[0].ny) * P.size() * sizeof(float);
+  if (10 * nx < 9 * 64 * strips && (bytes < 400.0 * (1 << 20) || share < 0.6)) return false;
+  return share > 0;
 }
 
 // One launch of K steps from time tt (step index k of the device clock).
@@ -564,8 +610,16 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
 //         8192   112.2 -> 103.7             171.6 -> 160.3
 // Alone means at this replay and the one before: of ensembles stepped in turn
 // and then waited for, the first to go on is not taken for a lone one.
+// Two steps per pass over memory and two branches exclude each other: the passes
+// are taken where they cover half of the chunk's steps, in the Hermite basis
+// always (us a step, passes / two branches; sums every 5, 10, no steps: Hermite
+// 64 x 160^2 18.7 / 18.8, 16.7 / 18.6, 15.4 / 18.3; f-norm 9 x 1003^2 118.8 /
+// 114.5, 112.2 / 110.5, 106.6 / 108.2, 256 x 200^2 163 / 179, 145 / 179, 136 /
+// 158).
 int Group::graph_branches(bool alone) const {
-  if (P.size() < 2 || multi_max || d_skacc || forced_launch) return 1;
+  if (P.size() < 2 || d_skacc || forced_launch) return 1;
+  const double share = pass_share((uint64_t)graph_chunk);
+  if (share > 0 && (!march_rows || basis == FLB_BASIS_HERMITE || share >= 0.5)) return 1;
   for (auto& h : hdesc)
     if (h.ntiles != hdesc[0].ntiles) return 1;
   return two_branches(compute, total_tiles, alone) ? 2 : 1;
@@ -598,7 +652,7 @@ int Group::capture_graph(int parts) {
   for (int k = 0; k < graph_chunk; ++k) {
     int pass[2];
     pass_pair((uint64_t)k, (uint64_t)(graph_chunk - k), false, &pass[0], &pass[1]);
-    if (pass[1]) {
+    if (pass[1] && parts == 1) {
       hipError_t e = hipSuccess;
       for (int i = 0; i < 2 && e == hipSuccess; ++i) {
         e = launch_pass((uint32_t)k, (uint64_t)k, pass[i], i);

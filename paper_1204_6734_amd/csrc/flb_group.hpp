@@ -72,6 +72,7 @@ struct Group {
   char* pop2 = nullptr;
   int multi_nt[2][kMultiMaxSteps + 1] = {{0}};
   int multi_max = 0;
+  std::vector<uint64_t> sample_intervals;  // the members' different ones
   // rows a wavefront of the two-step pass over a large lattice takes (0: the
   // launches of several steps are those of small lattices)
   int march_rows = 0;
@@ -115,6 +116,9 @@ struct Group {
   int abandon_capture(hipError_t e);
   void plan_multi(int cus);
   int plan_march(int cus) const;
+  double pass_share(uint64_t steps = 0) const;
+  bool passes_pay() const;
+  int sk_interval() const { return P.size() == 1 ? P[0].sk_every : 0; }
   bool take_second(size_t bytes) const;
   int pass_steps(uint64_t tt, uint64_t lim) const;
   bool pass_samples(uint64_t tt, int K) const;

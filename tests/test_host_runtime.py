@@ -161,3 +161,47 @@ assert streams() == 1
 L.sync()
 assert streams() == 2
 """)
+
+
+@pytest.mark.parametrize("nx,n,kw,second", [
+    (64, 1, dict(), True), (64, 1, dict(sample_every=1), True),
+    # sums of every step, where only steps without are taken together
+    (256, 1, dict(), True), (256, 1, dict(sample_every=1), False),
+    (256, 1, dict(sample_every=4), False), (256, 1, dict(sample_every=5), True),
+    (256, 1, dict(sk_every=5), True), (256, 1, dict(sk_every=4), False),
+    (3072, 1, dict(), True), (3072, 1, dict(sample_every=4), False),
+    (3072, 1, dict(sample_every=5), True), (3072, 1, dict(sample_every=1 << 30), True),
+    (160, 64, dict(basis=1), True), (160, 64, dict(basis=1, sample_every=2), False),
+    (160, 64, dict(basis=1, sample_every=5), True),
+    # strips that use four fifths of their lanes: 360 and 450 MiB
+    (256, 160, dict(), False), (256, 200, dict(), True), (256, 200, dict(sample_every=5), False),
+    (256, 200, dict(sample_every=10), True),
+])
+def test_second_buffers_only_where_they_are_used(program, nx, n, kw, second):
+    """A group allocates its populations twice exactly where launches of
+    several steps are made (the period of the sampling is stepped through)."""
+    program("""
+nx, n, kw = %d, %d, dict(%r)
+log()
+ps = [P(nx, nx, seed=k, **kw) for k in range(n)]
+L = F.Ensemble(ps) if n > 1 else F.Lattice(ps[0])
+big = max(int(x.split()[1]) for x in log("M"))
+pops = n * F.population_bytes(ps[0])
+L.step(40)
+several = log("K", "step_m")
+assert bool(several) == %r, several[:3]
+# one lattice needs what bytes_needed says and the second buffer; the members
+# of these ensembles take less than their populations beside them
+need = F.Lattice.bytes_needed(ps[0]) if n == 1 else 2 * pops
+assert (big > need) == %r and big < need + pops + 4096, (big, need, pops)
+""" % (nx, n, kw, second, second))
+
+
+@pytest.mark.parametrize("every,branches", [(0, 1), (1, 2), (2, 2), (5, 1), (10, 1)])
+def test_branches_where_a_chunk_holds_no_passes(program, every, branches):
+    program("""
+E = F.Ensemble([P(160, 160, basis=F.BASIS_HERMITE, seed=k, sample_every=%d) for k in range(64)],
+               graph_chunk=20)
+E.step(20)
+assert [x.split()[2] for x in log("G")] == ["%d"]
+""" % (every, branches))
