@@ -30,6 +30,10 @@ void Group::layout(Arena& a, bool second) {
   const int n = (int)P.size();
   d_slots = a.take<SlotDesc>(n);
   d_prefix = a.take<int>(n + 2);
+  if (plain_tiles) {
+    d_plain = a.take<SlotDesc>(n);
+    d_plain_prefix = a.take<int>(n + 2);
+  }
   d_clock = a.take<uint64_t>(1);
   d_err = a.take<int>(n);
   d_err_step = a.take<unsigned long long>(n);
@@ -118,6 +122,19 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
     prefix[s + 1] = prefix[s] + hdesc[s].ntiles;
   }
   total_tiles = prefix[n];
+  // The members' shape is one that suits the launches of several steps, which a
+  // group of this size does not take, and the order of the sums, which are the
+  // same for a member as alone, hangs on it.  Beyond the 256 MiB last-level
+  // cache the steps without sums are faster in 256 x 1 tiles (us a step, 64 x 4
+  // -> 256 x 1: 128 x 256^2 108.2 -> 104.4, 160 x 1000x60 132 -> 125, 600 x 256x100
+  // 206 -> 199; 64 x 256^2, 151 MiB, 47.7 -> 47.6); those with sums are not (129
+  // and 129).
+  if (small_lattice_tiles(ps[0]) &&
+      (double)population_elems(ps[0].nx, ps[0].ny) * n * sizeof(float) > 256.0 * (1 << 20)) {
+    SlotDesc d = hdesc[0];
+    set_tiles(&d, 1);
+    plain_tiles = d.ntiles;
+  }
   int lds = 0, cus = 0;
   HIPC(hipGetDevice(&device));
   HIPC(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
@@ -208,6 +225,15 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
       ctiles[c] = acc;
     }
     HIPC(hipMemcpy(d_slots, dev_desc.data(), n * sizeof(SlotDesc), hipMemcpyHostToDevice));
+    if (plain_tiles) {
+      std::vector<int> plain_prefix;
+      for (int c = 0; c < nclass; ++c)
+        for (int j = 0; j <= ccount[c]; ++j) plain_prefix.push_back(j * plain_tiles);
+      for (SlotDesc& d : dev_desc) set_tiles(&d, 1);
+      HIPC(hipMemcpy(d_plain, dev_desc.data(), n * sizeof(SlotDesc), hipMemcpyHostToDevice));
+      HIPC(hipMemcpy(d_plain_prefix, plain_prefix.data(), plain_prefix.size() * sizeof(int),
+                     hipMemcpyHostToDevice));
+    }
     std::vector<double*> close(2 * (size_t)n);
     for (int s = 0; s < n; ++s) {
       close[s] = d_partials[s];
@@ -337,10 +363,14 @@ hipError_t Group::launch_classes(uint32_t k, bool sample, int odd, LaunchCfg c, 
   for (int i = 0; i < nclass; ++i) {
     const int a = ccount[i] * part / parts, b = ccount[i] * (part + 1) / parts;
     if (a == b) continue;
+    const bool plain = plain_tiles && !sample;
+    const int tiles = plain ? (b - a) * plain_tiles
+                            : (parts == 1 ? ctiles[i] : (b - a) * hdesc[0].ntiles);
     const hipError_t e =
-        launch_step(storage, ccompute[i], basis, sample, odd, d_slots + cfirst[i] + a,
-                    d_prefix + cfirst[i] + i, b - a,
-                    parts == 1 ? ctiles[i] : (b - a) * hdesc[0].ntiles, d_clock, k, c, q);
+        launch_step(storage, ccompute[i], basis, sample, odd,
+                    (plain ? d_plain : d_slots) + cfirst[i] + a,
+                    (plain ? d_plain_prefix : d_prefix) + cfirst[i] + i, b - a, tiles, d_clock, k,
+                    c, q);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -31,6 +31,11 @@ struct Group {
   int nclass = 1;
   int ccompute[2] = {1, 0}, cfirst[2] = {0, 0}, ccount[2] = {0, 0}, ctiles[2] = {0, 0};
   std::vector<int> corder;  // device position -> member
+  // Steps without sums may use another tile shape than those with (Group::init):
+  // descriptors and prefix sums of the same form, tiles of one member.
+  int plain_tiles = 0;  // 0: the shape of the steps with sums
+  SlotDesc* d_plain = nullptr;
+  int* d_plain_prefix = nullptr;
   hipStream_t st = nullptr;
   bool own_stream = false, own_mem = false;
   void* dev = nullptr;

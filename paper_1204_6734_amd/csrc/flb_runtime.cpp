@@ -309,6 +309,21 @@ uint32_t row_pitch(int nx) { return (uint32_t)((nx + kTileX - 1) / kTileX * kTil
 // Elements of a lattice's population storage (nine plane rows per row).
 size_t population_elems(int nx, int ny) { return (size_t)9 * ny * row_pitch(nx); }
 
+// Whether 256 x 1 tiles would leave the last tile of a row mostly empty.
+static bool last_tile_empty(int nx) {
+  const int64_t quarters = (nx + kTileX - 1) / kTileX;
+  return 10 * ((quarters + kTileY - 1) / kTileY * kTileY) > 11 * quarters;
+}
+// Whether 64 x 4 tiles are taken for the launches of several steps alone.
+bool small_lattice_tiles(const flb_params& p) {
+  return p.precision == FLB_FP32_SHIFTED && p.nx >= kWideTileMinNx && !last_tile_empty(p.nx) &&
+         (uint64_t)p.nx * p.ny <= kWideTileMinSites;
+}
+static void tile_counts(int nx, int ny, int wide, int* tiles_x, int* ntiles) {
+  const int tw = wide ? kTileX * kTileY : kTileX, th = wide ? 1 : kTileY;
+  *tiles_x = (nx + tw - 1) / tw;
+  *ntiles = *tiles_x * ((ny + th - 1) / th);
+}
 // Tile shape and count: 256 x 1 tiles (four wavefronts along a row) on rows
 // of at least kWideTileMinNx sites, whose wavefronts then read longer
 // stretches of one row (measured faster on large lattices), else 64 x 4.
@@ -320,15 +335,12 @@ size_t population_elems(int nx, int ny) { return (size_t)9 * ny * row_pitch(nx);
 //    their workgroup's slots (64 lattices of 300 x 200, eight wavefronts a
 //    row for five of sites: FP32 57 -> 45 us a step, FP64 130 -> 103).
 void tile_shape(const flb_params& p, int* wide, int* tiles_x, int* ntiles) {
-  const int nx = p.nx, ny = p.ny;
-  const int64_t quarters = (nx + kTileX - 1) / kTileX;
-  const int64_t padded = (quarters + kTileY - 1) / kTileY * kTileY;
   const bool free_order = p.precision == FLB_FP32_SHIFTED || p.sample_every == 0;
-  const bool small = p.precision == FLB_FP32_SHIFTED && (uint64_t)nx * ny <= kWideTileMinSites;
-  *wide = nx >= kWideTileMinNx && !small && !(free_order && 10 * padded > 11 * quarters) ? 1 : 0;
-  const int tw = *wide ? kTileX * kTileY : kTileX, th = *wide ? 1 : kTileY;
-  *tiles_x = (nx + tw - 1) / tw;
-  *ntiles = *tiles_x * ((ny + th - 1) / th);
+  *wide = p.nx >= kWideTileMinNx && !small_lattice_tiles(p) &&
+                  !(free_order && last_tile_empty(p.nx))
+              ? 1
+              : 0;
+  tile_counts(p.nx, p.ny, *wide, tiles_x, ntiles);
 }
 
 // Division by d >= 1 as a multiply-shift (Granlund-Montgomery, round-up
@@ -344,12 +356,20 @@ void magic_div(uint32_t d, uint32_t* magic, uint32_t* shift) {
   *shift = (uint32_t)k;
 }
 
+// Gives a slot the tiles of either shape.
+void set_tiles(SlotDesc* d, int wide) {
+  d->wide = wide;
+  tile_counts(d->nx, d->ny, wide, &d->tiles_x, &d->ntiles);
+  magic_div((uint32_t)d->tiles_x, &d->tx_magic, &d->tx_shift);
+}
+
 void fill_slot(const flb_params* p, SlotDesc* d) {
   d->nx = p->nx;
   d->ny = p->ny;
   d->pitch = row_pitch(p->nx);
-  tile_shape(*p, &d->wide, &d->tiles_x, &d->ntiles);
-  magic_div((uint32_t)d->tiles_x, &d->tx_magic, &d->tx_shift);
+  int tiles_x, ntiles;
+  tile_shape(*p, &d->wide, &tiles_x, &ntiles);
+  set_tiles(d, d->wide);
   magic_div(p->sample_every > 0 ? (uint32_t)p->sample_every : 1u, &d->se_magic, &d->se_shift);
   magic_div(p->sk_every > 0 ? (uint32_t)p->sk_every : 1u, &d->sk_magic, &d->sk_shift);
   d->k0 = (uint32_t)p->seed;

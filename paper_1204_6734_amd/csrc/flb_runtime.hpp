@@ -32,6 +32,8 @@ inline bool two_branches(int compute, int tiles, bool alone) {
 uint32_t row_pitch(int nx);
 size_t population_elems(int nx, int ny);
 void tile_shape(const flb_params& p, int* wide, int* tiles_x, int* ntiles);
+void set_tiles(SlotDesc* d, int wide);
+bool small_lattice_tiles(const flb_params& p);
 void magic_div(uint32_t d, uint32_t* magic, uint32_t* shift);
 void fill_slot(const flb_params* p, SlotDesc* d);
 Shift9 slot_shift(const SlotDesc& d);

@@ -3,7 +3,7 @@
 // libflb.so, whose calls then come here.  "Device" memory is untouched host
 // memory, kernels are log lines, and work is finished by waiting for it.
 //
-// Log, one line each: K <stream> <kernel> (a launch), C ... (the same, into a
+// Log, one line each: K <stream> <kernel> <grid> (a launch), C ... (the same, into a
 // captured graph), G <stream> <branches> (a replay), M <bytes> (an allocation), S <stream>
 // <steps> (a wait for a stream with that many step launches pending), P <stream>
 // (an event asked for while step launches recorded before it are pending).
@@ -97,7 +97,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void**, size_t lds, hi
     return error(hipErrorInvalidConfiguration);
   if (fail_in > 0 && n.find(fail_name) != std::string::npos && --fail_in == 0)
     return error(hipErrorLaunchFailure);
-  put((s->capturing ? "C " : "K ") + std::to_string(s->id) + " " + n);
+  put((s->capturing ? "C " : "K ") + std::to_string(s->id) + " " + n + " " +
+      std::to_string(g.x));
   if (s->capturing) captured.insert(s);
   if (!s->capturing && n.find("step") != std::string::npos) ++s->steps;
   return hipSuccess;

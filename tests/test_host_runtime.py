@@ -205,3 +205,23 @@ E = F.Ensemble([P(160, 160, basis=F.BASIS_HERMITE, seed=k, sample_every=%d) for 
 E.step(20)
 assert [x.split()[2] for x in log("G")] == ["%d"]
 """ % (every, branches))
+
+
+@pytest.mark.parametrize("nx,ny,n,tiles,tiles_summed", [
+    (256, 99, 350, 99, 100),  # 304 MiB: 256 x 1 tiles without sums, 64 x 4 with
+    (256, 99, 290, 100, 100),  # 252 MiB
+    (257, 99, 350, 125, 125),  # 256 x 1 tiles would be mostly empty
+    (256, 257, 150, 257, 257),  # more than 65536 sites: 256 x 1 throughout
+])
+def test_tile_shapes_of_ensembles_beyond_the_cache(program, nx, ny, n, tiles, tiles_summed):
+    program("""
+E = F.Ensemble([P(%d, %d, seed=k, ux0=0.3 if k < 20 else 0.0, sample_every=4)
+                for k in range(%d)])
+n = len(E.params)
+E.set_launch(1, 0)
+log()
+E.step(2)
+grids = [int(x.split()[3]) for x in log("K", "step_kernel")]
+want = [%d, %d]  # the step with sums comes first; two compute classes
+assert grids == [(n - 20) * want[0], 20 * want[0], (n - 20) * want[1], 20 * want[1]], grids
+""" % (nx, ny, n, tiles_summed, tiles))
