@@ -512,12 +512,11 @@ int Group::plan_march(int cus) const {
   return waves >= (hermite ? 16.0 : 64.0) * cus ? rows : rows / 2;
 }
 
-// Whether a second population buffer of this size is taken: small ones always,
-// larger ones where seven eighths of the device's memory stay free beside both
-// buffers (so that programs which fill the memory find it as large as before;
-// 16384 x 16384 takes twice 9.7 of 288 GB).
+// Whether a second population buffer of this size is taken: where seven eighths
+// of the device's memory stay free beside both buffers (16384 x 16384 takes twice
+// 9.7 of 288 GB).  A program that fills the memory, with one lattice or with
+// thousands of small ones, gives at most a sixteenth of it to second buffers.
 bool Group::take_second(size_t bytes) const {
-  if (bytes <= ((size_t)256 << 20)) return true;
   size_t freeb = 0, total = 0;
   if (hipMemGetInfo(&freeb, &total) != hipSuccess) {
     (void)hipGetLastError();

@@ -225,3 +225,21 @@ grids = [int(x.split()[3]) for x in log("K", "step_kernel")]
 want = [%d, %d]  # the step with sums comes first; two compute classes
 assert grids == [(n - 20) * want[0], 20 * want[0], (n - 20) * want[1], 20 * want[1]], grids
 """ % (nx, ny, n, tiles_summed, tiles))
+
+
+def test_a_full_device_holds_nearly_as_many_small_lattices(program):
+    """Second buffers stop being taken once an eighth of the memory is in use:
+    a program that fills the device gives them a sixteenth of it at most."""
+    program("""
+one = F.Lattice.bytes_needed(P(64, 64))  # a lattice that takes a second buffer
+total = 400 * one
+fake.fake_memory(total)
+held = []
+try:
+    while True:
+        held.append(F.Lattice(P(64, 64)))
+except F.FlbError as e:
+    assert e.code == F.E_OOM
+assert len(held) >= 400 * 15 // 16, len(held)
+assert sum(int(x.split()[1]) > one + one // 4 for x in log("M")) > 5
+""")
