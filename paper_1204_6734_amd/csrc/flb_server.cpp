@@ -408,7 +408,12 @@ int flb_server::pump(int max_chunks, int* did) {
     if (active.empty()) break;
     const double t0 = now();
     int rc = run_chunk();
-    if (rc != FLB_OK) return rc;
+    if (rc != FLB_OK) {
+      // the next chunk's tables go to st alone: nothing of this one may still
+      // run on the second stream
+      (void)hipStreamSynchronize(st2);
+      return rc;
+    }
     rc = retire();
     if (rc != FLB_OK) return rc;
     std::lock_guard<std::mutex> lk(mu);

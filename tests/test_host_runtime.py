@@ -243,3 +243,27 @@ except F.FlbError as e:
 assert len(held) >= 400 * 15 // 16, len(held)
 assert sum(int(x.split()[1]) > one + one // 4 for x in log("M")) > 5
 """)
+
+
+@pytest.mark.parametrize("launch", [1, 2, 5])
+def test_a_failed_chunk_leaves_nothing_on_the_second_stream(program, launch):
+    """The next chunk writes the tables that the second stream's launches of
+    the failed one read."""
+    program("""
+S = F.Server(1 << 30, threaded=False, chunk_steps=4)
+for k in range(40):
+    S.submit(P(128, 128, seed=k), 12)
+S.pump(1)
+second = {x.split()[1] for x in log("K", "step_kernel")}
+assert len(second) == 2
+fake.fake_fail(b"step_kernel", %d)
+try:
+    S.pump(1)
+    raise SystemExit("no failure")
+except F.FlbError:
+    pass
+lines = [x for x in log("KS") if x[0] == "S" or "step_kernel" in x]
+for s in sorted(second)[1:]:  # the second stream is the later one
+    last = [x[0] for x in lines if x.split()[1] == s]
+    assert last == [] or last[-1] == "S", lines
+""" % launch)
