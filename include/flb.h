@@ -351,6 +351,10 @@ int flb_lattice_set_launch(flb_lattice* L, const flb_launch_config* c);
 int flb_ensemble_set_launch(flb_ensemble* E, const flb_launch_config* c);
 int flb_lattice_get_launch(flb_lattice* L, flb_launch_config* c);
 int flb_ensemble_get_launch(flb_ensemble* E, flb_launch_config* c);
+/* Steps since creation that launches of several steps took (the others were
+ * launched one by one); counted as they are enqueued. */
+int flb_lattice_pass_steps(flb_lattice* L, uint64_t* steps);
+int flb_ensemble_pass_steps(flb_ensemble* E, uint64_t* steps);
 
 /* ---------------------------------------------------------- D3Q19 lattices
  * The same step on the D3Q19 velocity set (the paper's construction carried

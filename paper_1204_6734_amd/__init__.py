@@ -136,6 +136,8 @@ _SIGS = {
     "flb_ensemble_set_launch": [C.c_void_p, C.POINTER(LaunchConfig)],
     "flb_lattice_get_launch": [C.c_void_p, C.POINTER(LaunchConfig)],
     "flb_ensemble_get_launch": [C.c_void_p, C.POINTER(LaunchConfig)],
+    "flb_lattice_pass_steps": [C.c_void_p, C.POINTER(C.c_uint64)],
+    "flb_ensemble_pass_steps": [C.c_void_p, C.POINTER(C.c_uint64)],
     "flb3_lattice_create": [C.POINTER(Params3), C.c_void_p, C.POINTER(C.c_void_p)],
     "flb3_lattice_set_populations": [C.c_void_p, C.POINTER(C.c_double), C.c_uint64],
     "flb3_lattice_step": [C.c_void_p, C.c_uint64],
@@ -286,6 +288,13 @@ class _Tunable:
         c = LaunchConfig()
         _check(getattr(load(), f"flb_{self._kind}_get_launch")(self.h, C.byref(c)), "get_launch")
         return {"tiles_per_block": c.tiles_per_block, "grid_blocks": c.grid_blocks}
+
+    def pass_steps(self) -> int:
+        """Steps since creation that launches of several steps took
+        (flb_*_pass_steps)."""
+        n = C.c_uint64()
+        _check(getattr(load(), f"flb_{self._kind}_pass_steps")(self.h, C.byref(n)), "pass_steps")
+        return int(n.value)
 
 
 class Lattice(_Tunable):

@@ -678,6 +678,7 @@ int Group::capture_graph(int parts) {
       e = hipStreamWaitEvent(branch[i], joined[0], 0);
     if (e != hipSuccess) return abandon_capture(e);
   }
+  graph_passed[parts - 1] = 0;
   for (int k = 0; k < graph_chunk; ++k) {
     int pass[2];
     pass_pair((uint64_t)k, (uint64_t)(graph_chunk - k), false, &pass[0], &pass[1]);
@@ -689,6 +690,7 @@ int Group::capture_graph(int parts) {
           e = launch_sk_sample(storage, d_z, d_zt, d_skacc, P[0].nx, P[0].ny, d_twx, d_twy,
                                max_lds, st);
         k += pass[i];
+        graph_passed[parts - 1] += (uint64_t)pass[i];
       }
       if (e != hipSuccess) return abandon_capture(e);
       --k;  // the loop's own step
@@ -752,6 +754,7 @@ int Group::step(uint64_t nsteps) {
         rc = after_step(t + k, true);
         if (rc != FLB_OK) return rc;
       }
+      passed += graph_passed[parts - 1];
       t += K;
       done += K;
       continue;
@@ -775,6 +778,7 @@ int Group::step(uint64_t nsteps) {
           for (int j = 0; j < pass[i] && rc == FLB_OK; ++j) rc = after_step(t + k + (uint64_t)j);
           if (rc != FLB_OK) return rc;
           k += (uint64_t)pass[i];
+          passed += (uint64_t)pass[i];
         }
         --k;  // the loop's own step
         continue;
@@ -1249,6 +1253,12 @@ int flb_lattice_kernel_time(flb_lattice* L, double* ms, uint64_t* launches) {
   NEED(L);
   return L->g.kernel_time(ms, launches);
 }
+int flb_lattice_pass_steps(flb_lattice* L, uint64_t* steps) {
+  NEED(L);
+  if (!steps) return flb::set_error(FLB_E_ARG, "null output");
+  *steps = L->g.passed;
+  return FLB_OK;
+}
 void flb_lattice_destroy(flb_lattice* L) { delete L; }
 
 int flb_ensemble_create(const flb_params* ps, int32_t n, void* hip_stream, flb_ensemble** out) {
@@ -1304,6 +1314,12 @@ int flb_ensemble_profile(flb_ensemble* E, int32_t on) {
 int flb_ensemble_kernel_time(flb_ensemble* E, double* ms, uint64_t* launches) {
   NEED(E);
   return E->g.kernel_time(ms, launches);
+}
+int flb_ensemble_pass_steps(flb_ensemble* E, uint64_t* steps) {
+  NEED(E);
+  if (!steps) return flb::set_error(FLB_E_ARG, "null output");
+  *steps = E->g.passed;
+  return FLB_OK;
 }
 void flb_ensemble_destroy(flb_ensemble* E) { delete E; }
 

@@ -81,12 +81,14 @@ struct Group {
   // rows a wavefront of the two-step pass over a large lattice takes (0: the
   // launches of several steps are those of small lattices)
   int march_rows = 0;
+  uint64_t passed = 0;  // steps taken so since creation
   // graphs: the captured chunk in one branch and in two, each captured when
   // it is first replayed (graph_branches)
   int graph_chunk = 0;
   static constexpr int kMaxBranches = 2;
   hipGraph_t graph[kMaxBranches] = {nullptr};
   hipGraphExec_t graph_exec[kMaxBranches] = {nullptr};
+  uint64_t graph_passed[kMaxBranches] = {0};  // its steps in launches of several
   AtWork at_work;
   bool shared = false;  // something else was at work at the last replay
   // side branches of the captured graph: their streams (from 1) and the

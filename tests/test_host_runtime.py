@@ -267,3 +267,36 @@ for s in sorted(second)[1:]:  # the second stream is the later one
     last = [x[0] for x in lines if x.split()[1] == s]
     assert last == [] or last[-1] == "S", lines
 """ % launch)
+
+
+def test_pass_steps_counts_launches_of_several_steps(program):
+    program("""
+for chunk in (0, 12):
+    L = F.Lattice(P(64, 64, sample_every=3, block_steps=5))
+    L.set_graph_chunk(chunk)
+    E = F.Ensemble([P(32, 30, seed=k) for k in range(4)], graph_chunk=chunk)
+    for G in (L, E):
+        total = 0
+        for n in (1, 7, 24, 5, 36):
+            G.step(n)
+            total += n
+            assert 0 <= G.pass_steps() <= total
+        assert G.pass_steps() > total // 2
+        before = G.pass_steps()
+        G.set_launch(1, 0)
+        G.step(40)
+        assert G.pass_steps() == before
+S = F.Lattice(P(64, 64, sample_every=1, block_steps=1))  # every step closes a block
+S.step(20)
+assert S.pass_steps() == 0
+L = F.Lattice(P(64, 64))
+log()
+L.step(41)
+assert len(log("K", "step_kernel")) == 41 - L.pass_steps()
+try:
+    F._check(F.load().flb_lattice_pass_steps(L.h, None), "")
+    raise SystemExit("accepted")
+except F.FlbError as e:
+    assert e.code == F.E_ARG
+assert F.load().flb_ensemble_pass_steps(None, None) == F.E_ARG
+""")
