@@ -18,9 +18,10 @@ the board's power limit settles the step at.
 
 Prints one JSON line: MLUPS (lattice-site updates per second / 1e6) over
 the timed steps, the step kernel's achieved HBM bandwidth against the
-8 TB/s peak (36 bytes per site update, the populations being read and
-written once for two steps; pct_hbm_roofline is against the rate that 72
-bytes, one pass per step, allow), a served-requests measurement (solves/s and p50/p99
+8 TB/s peak (72 bytes per site update, 36 in the launches that read and write
+the populations once for two steps, as the library counts them;
+pct_hbm_roofline is the same share for the whole path, and
+pct_of_one_pass_rate the updates against those that 72 bytes each allow), a served-requests measurement (solves/s and p50/p99
 latency of mixed Poisson-arriving requests through the continuous-batching
 server, next to the plain FP64 one-lattice-per-launch path on the same
 arrivals), and the FP64 CPU oracle's rate on a bounded sample of the
@@ -50,6 +51,7 @@ D3Q19_VALU_PER_SITE = 1924
 # the same of the two-step pass of the large D2Q9 FP32 lattice, per 64 site
 # updates (halo lanes and rows included), profiles/step_fp32_8192_counters.md
 MARCH_VALU_PER_SITE = 418.5
+STEP_VALU_PER_SITE = 378  # and of one step per launch, both phases averaged
 # FP32 floating-point operations per site of that D3Q19 kernel (its variant for
 # one relaxation time, which this workload's tau = 1 selects), counted in its
 # gfx950 code: FMAs 2 each (1348 v_fma/v_fmac/v_fmamk), multiplies, adds and
@@ -93,8 +95,8 @@ def kernel_hash() -> str:
 
 
 def traffic_from_profiles(name: str):
-    """HBM bytes per launch (two steps, where a pass takes two) from the committed counter summary, if it was
-    taken on the current kernel sources."""
+    """HBM bytes per launch (two steps, where a pass takes two) from the
+    committed counter summary, if it was taken on the current kernel sources."""
     path = os.path.join(ROOT, "profiles", f"{name}_traffic.json")
     if not os.path.exists(path):
         return None
@@ -247,19 +249,16 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
     settle.close()
     L.profile(True)
     L.kernel_time()  # reset
-    tw0 = L.t
+    tw0, passed0 = L.t, L.pass_steps()
     t0 = time.perf_counter()
     log = run(steps)
     L.sync()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    passed = L.pass_steps() - passed0  # steps that passes of two steps took
     kms, launches = L.kernel_time()
     L.profile(False)
     sites = nx * nx
-    # large FP32 lattices take two steps per pass over memory between samples,
-    # unless --launch fixes the shape of one-step launches (Group::plan_march)
-    two = (fp32 and launch is None and sample_every == 0 and
-           36 * sites >= (32 if basis == "hermite" else 300) << 20)
     # structure-factor samples and mode logs that fell in the timed steps
     n_sk = (len([t for t in range(tw0, tw0 + steps) if t % every == 0]) if every > 0 else 0)
     with_sk = None
@@ -279,7 +278,8 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
         with_sk = {"steps": every, "sk_samples": 1, "mode_logs": 1,
                    "ms_per_step": round(dt1 * 1e3 / every, 4),
                    "mlups": round(sites * every / dt1 / 1e6, 1)}
-    return {"sites": sites, "dt": dt, "steps_per_pass": 2 if two else 1, "kernel_ms": kms / max(launches, 1), "launches": launches,
+    return {"sites": sites, "dt": dt, "pass_steps": passed, "steps": steps,
+            "kernel_ms": kms / max(launches, 1), "launches": launches,
             "mode_log": [abs(z) for z in log[-3:]], "probes": probes, "settle_steps": settle_steps,
             "sk_in_window": n_sk, "mode_logs_in_window": len(log), "with_sk": with_sk,
             "launch": {"chosen": L.get_launch(), "candidates": tune},
@@ -299,14 +299,59 @@ def run_large(F, torch, steps: int, warmup: int, nx: int = 8192, every: int = 10
                        "parallelism": "single GPU"},
             "dtype": "f32" if fp32 else "f64",
             # FP32 storage computes the collision in FP64 above |u0| = 0.25
-            "kernel_label": "step_march_kernel<%s>" % bname if two else "step_kernel<%s,%s>" % (
-                ("float,float" if abs(ux0) <= 0.25 else "float,double") if fp32
-                else "double,double", bname) +
+            "kernel_label": " and ".join(
+                (["step_march_kernel<%s>" % bname] if passed else []) +
+                (["step_kernel<%s,%s>" % (
+                    ("float,float" if abs(ux0) <= 0.25 else "float,double") if fp32
+                    else "double,double", bname)] if passed < steps else [])) +
                 (f" (correlator-sampling variant every {sample_every} steps)"
                  if sample_every > 0 else ""),
             "kernel_name": f"step_{precision}_{nx}" + ("" if basis == "fnorm" else f"_{basis}") +
                            ("_fp64compute" if fp32 and abs(ux0) > 0.25 else "") +
                            (f"_sample{sample_every}" if sample_every > 0 else "")}
+
+
+def large_rooflines(r: dict) -> dict:
+    """The share of the HBM peak that run_large's steps reached, by the bytes
+    they moved: a pass of two steps reads and writes the populations once."""
+    share = r["pass_steps"] / r["steps"]
+    bps = BYTES_PER_SITE[r["dtype"]]
+    moved = bps * (1 - share / 2)
+    achieved = moved * r["sites"] / (r["kernel_ms"] * 1e-3) / 1e9
+    rate = r["sites"] * r["steps"] / r["dt"]
+    # the step's memory traffic with no arithmetic (same layout, tiles and
+    # addressing): the practical ceiling of its access pattern; and a plain
+    # contiguous copy of the population bytes: the device's streaming ceiling
+    copy_ms = r["probes"]["copy_ms"]
+    copy_gbps = bps * r["sites"] / (copy_ms * 1e-3) / 1e9
+    stream_bytes, stream_ms = r["probes"]["stream_bytes"], r["probes"]["stream_ms"]
+    stream_gbps = 2 * stream_bytes / (stream_ms * 1e-3) / 1e9
+    out = {
+        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+                     # the counted launches are passes of two steps
+                     "traffic": traffic_from_profiles(r["kernel_name"]) if share else None,
+                     "kernel": r["kernel_label"],
+                     "bytes_per_site": round(moved, 2), "pass_steps": r["pass_steps"],
+                     "kernel_ms": round(r["kernel_ms"], 4),
+                     "launches": r["launches"],
+                     "copy_probe": {"GBps": round(copy_gbps, 1), "ms": round(copy_ms, 4),
+                                    "frac_of_peak": round(copy_gbps / HBM_PEAK_GBS, 4),
+                                    "kernel_frac_of_copy": round(achieved / copy_gbps, 4),
+                                    "what": "the step's loads and stores, no arithmetic"},
+                     "stream_copy": {"GBps": round(stream_gbps, 1), "ms": round(stream_ms, 4),
+                                     "frac_of_peak": round(stream_gbps / HBM_PEAK_GBS, 4),
+                                     "what": "contiguous copy of the population bytes, "
+                                             "16 B per thread"}},
+        "pct_hbm_roofline": round(100 * rate * moved / (HBM_PEAK_GBS * 1e9), 2),
+        "pct_of_one_pass_rate": round(100 * rate * bps / (HBM_PEAK_GBS * 1e9), 2)}
+    if share and r["config"]["basis"] == "fnorm_local" and not r["config"]["sample_every"]:
+        # what bounds the passes: the issue of their vector instructions
+        per_site = share * MARCH_VALU_PER_SITE + (1 - share) * STEP_VALU_PER_SITE
+        out["valu_issue"] = {
+            "wavefront_instructions_per_site": round(per_site, 1),
+            "issue_ms_at_4_cycles": round(per_site * r["sites"] / 64 / VALU_ISSUE_PEAK * 1e3, 4)}
+    return out
 
 
 def run_ensemble(F, torch, steps: int, warmup: int, n: int = 64, side: int = 128,
@@ -572,49 +617,19 @@ def main():
                   launch=launch, basis=args.basis, precision=args.precision, ux0=args.ux0,
                   sample_every=args.sample_every)
     mlups = r["sites"] * args.steps / r["dt"] / 1e6
-    bps = BYTES_PER_SITE[r["dtype"]]
-    # bytes a step moves: a pass of two steps reads and writes once
-    moved = bps // r["steps_per_pass"]
-    achieved = moved * r["sites"] / (r["kernel_ms"] * 1e-3) / 1e9
-    traffic = traffic_from_profiles(r["kernel_name"])
-    # the step's memory traffic with no arithmetic (same layout, tiles and
-    # addressing): the practical ceiling of its access pattern; and a plain
-    # contiguous copy of the population bytes: the device's streaming ceiling
-    copy_ms = r["probes"]["copy_ms"]
-    copy_gbps = bps * r["sites"] / (copy_ms * 1e-3) / 1e9
-    stream_bytes, stream_ms = r["probes"]["stream_bytes"], r["probes"]["stream_ms"]
-    stream_gbps = 2 * stream_bytes / (stream_ms * 1e-3) / 1e9
+    roof = large_rooflines(r)
     out = {
         "metric": "fluct. D2Q9 MLUPS, % of HBM roofline; served solves/s + p99 latency",
         "value": round(mlups, 1), "unit": "MLUPS", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": round(r["dt"] * 1e3 / args.steps, 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": r["dtype"],
         "data": "synthetic", "config": r["config"],
-        "roofline": {"bound": "hbm" if r["steps_per_pass"] == 1 else "alu",
-                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel": r["kernel_label"],
-                     "bytes_per_site": moved, "steps_per_pass": r["steps_per_pass"],
-                     "kernel_ms": round(r["kernel_ms"], 4),
-                     "launches": r["launches"],
-                     "copy_probe": {"GBps": round(copy_gbps, 1), "ms": round(copy_ms, 4),
-                                    "frac_of_peak": round(copy_gbps / HBM_PEAK_GBS, 4),
-                                    "kernel_frac_of_copy": round(achieved / copy_gbps, 4),
-                                    "what": "the step's loads and stores, no arithmetic"},
-                     "stream_copy": {"GBps": round(stream_gbps, 1), "ms": round(stream_ms, 4),
-                                     "frac_of_peak": round(stream_gbps / HBM_PEAK_GBS, 4),
-                                     "what": "contiguous copy of the population bytes, "
-                                             "16 B per thread"}},
-        "pct_hbm_roofline": round(100 * mlups * 1e6 * bps / (HBM_PEAK_GBS * 1e9), 2),
+        **roof,
         "launch": dict(r["launch"], settle_steps=r["settle_steps"]),
         "structure_factor": {"sk_every": args.sk_every, "sk_samples_in_window": r["sk_in_window"],
                              "mode_logs_in_window": r["mode_logs_in_window"],
                              "with_sk": r["with_sk"]},
     }
-    if r["steps_per_pass"] == 2 and args.basis == "fnorm":
-        instr = MARCH_VALU_PER_SITE * r["sites"] / 64
-        out["valu_issue"] = {"wavefront_instructions_per_site": MARCH_VALU_PER_SITE,
-                             "issue_ms_at_4_cycles": round(instr / VALU_ISSUE_PEAK * 1e3, 4)}
     if not args.no_serving:
         out["serving"] = run_serving(F, torch, nreq=args.requests or 40)
     if not args.no_cpu_baseline:
