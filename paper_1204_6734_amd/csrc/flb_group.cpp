@@ -428,11 +428,10 @@ uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
 }
 
 // ------------------------------------------------- several steps per launch
-// Tiles per workgroup for every number of steps a launch may take.  Several
-// steps pay while a step is held by latency, that is while the chip is not
-// full: at one tile per workgroup (the halo is cheapest to recompute when
-// nothing else wants the SIMDs; two tiles measured slower), up to one
-// workgroup per CU.  Measured (us a step, one step per launch -> this; without
+// The numbers of steps that launches take.  Several steps pay while a step is
+// held by latency, that is while the chip is not full: at one tile per
+// workgroup (the halo is cheapest to recompute when nothing else wants the
+// SIMDs; two tiles measured slower), up to one workgroup per CU.  Measured (us a step, one step per launch -> this; without
 // / with sums of every step): FP32 21^2 2.9 -> 1.8 / 4.0 -> 2.2, 64^2 2.9 ->
 // 2.3 / 4.1 -> 2.9, 256^2 (256 tiles) 3.2 -> 2.8 / 4.1 -> 3.4, but 256 x 320
 // (320 tiles) 3.6 -> 4.7 / 4.7 -> 6.3.  Lattices of two or more rows per
@@ -455,10 +454,10 @@ uint64_t Group::steps_to_close(uint64_t tt, uint64_t skip) const {
 // two (5), 8.3 four (9).
 void Group::plan_multi(int cus) {
   multi_max = 0;
-  std::fill(&multi_nt[0][0], &multi_nt[0][0] + 2 * (kMultiMaxSteps + 1), 0);
+  std::fill(&multi_takes[0][0], &multi_takes[0][0] + 2 * (kMultiMaxSteps + 1), false);
   march_rows = plan_march(cus);
   if (march_rows) {
-    multi_nt[0][2] = 1;  // steps without sums only
+    multi_takes[0][2] = true;  // steps without sums only
     multi_max = 2;
     return;
   }
@@ -470,12 +469,12 @@ void Group::plan_multi(int cus) {
       narrow && (compute == 1 || nx <= kTileX / 4) && total_tiles <= cus ? 6 : 4;
   for (int sample = 0; sample < 2; ++sample)
     for (int K = 2; K <= most; K += 2) {
-      if (!multi_fits(storage, compute, sample != 0, nx, K, 1, max_lds)) continue;
-      const double waves = (double)total_tiles * multi_waves(compute, sample != 0, nx, K, 1);
+      if (!multi_fits(storage, compute, sample != 0, nx, K, max_lds)) continue;
+      const double waves = (double)total_tiles * multi_waves(compute, sample != 0, nx, K);
       if (sample && !narrow ? 2 * total_tiles > cus
                             : waves > (compute == 0 ? 4.9 : sample ? 8.3 : 7.0) * cus)
         continue;
-      multi_nt[sample][K] = 1;
+      multi_takes[sample][K] = true;
       multi_max = std::max(multi_max, K);
     }
 }
@@ -530,7 +529,7 @@ bool Group::take_second(size_t bytes) const {
 int Group::pass_steps(uint64_t tt, uint64_t lim) const {
   if (const uint64_t sk = (uint64_t)sk_interval()) lim = std::min(lim, sk - tt % sk);
   for (int K = multi_max; K >= 2; K -= 2)
-    if ((uint64_t)K <= lim && multi_nt[pass_samples(tt, K)][K]) return K;
+    if ((uint64_t)K <= lim && multi_takes[pass_samples(tt, K)][K]) return K;
   return 0;
 }
 
@@ -551,7 +550,7 @@ void Group::pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb)
   if (!multi_max || forced_launch || (tt & 1)) return;
   const uint64_t m = closes ? steps_to_close(tt, 0) : ~0ull;
   for (int K = pass_steps(tt, std::min(left, m)); K >= 2; K -= 2) {
-    if (!multi_nt[pass_samples(tt, K)][K]) continue;
+    if (!multi_takes[pass_samples(tt, K)][K]) continue;
     const uint64_t m2 = closes ? steps_to_close(tt, (uint64_t)K) - (uint64_t)K : ~0ull;
     *ka = K;
     *kb = pass_steps(tt + (uint64_t)K, std::min(left - (uint64_t)K, m2));
@@ -609,7 +608,7 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
   for (int i = 0; i < nclass; ++i) {
     const hipError_t e =
         launch_step_multi(storage, ccompute[i], basis, sample, d_slots + cfirst[i], ccount[i],
-                          P[0].nx, P[0].ny, K, multi_nt[sample][K], flip, d_clock, k, st);
+                          P[0].nx, P[0].ny, K, flip, d_clock, k, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

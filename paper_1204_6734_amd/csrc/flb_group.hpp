@@ -72,10 +72,10 @@ struct Group {
   bool forced_launch = false;
   int device = 0;
   // several steps per launch: the second population buffer (null: one step
-  // per launch) and, without and with correlator sums, the tiles per workgroup
-  // for each number of steps (0: not taken)
+  // per launch) and, without and with correlator sums, the numbers of steps
+  // that launches take
   char* pop2 = nullptr;
-  int multi_nt[2][kMultiMaxSteps + 1] = {{0}};
+  bool multi_takes[2][kMultiMaxSteps + 1] = {{false}};
   int multi_max = 0;
   std::vector<uint64_t> sample_intervals;  // the members' different ones
   // rows a wavefront of the two-step pass over a large lattice takes (0: the

@@ -31,7 +31,7 @@
 
 namespace flb {
 
-// Row stride of the LDS populations: 64 columns and up to four halo columns
+// Row stride of the LDS populations: 64 columns and up to three halo columns
 // on each side.  Value i of (row, column) at ((9 row + i) kRS + column), so
 // that the nine values and the neighbours' rows are immediate offsets of one
 // of three addresses (columns x - 1, x, x + 1).
@@ -134,7 +134,7 @@ struct MultiShape {
   int groups;                    // workgroups of one lattice
   uint32_t gr_magic, gr_shift;   // division by groups
   uint32_t tx_magic, tx_shift;   // and by tiles_x
-  int K, nt;
+  int K;
   int ncw, nnw;                  // colliding and drawing wavefronts
   int rpw;                       // lattice rows of a wavefront (nx <= 64)
   uint32_t nx_magic;             // lane / nx = (lane nx_magic) >> 16
@@ -150,8 +150,9 @@ constexpr bool draws_apart() {
   return sizeof(R) == 8;
 }
 
-// Workgroup: nt tiles of 64 x 4 sites stacked in y (all of the lattice's
-// columns when nx <= 64, then without an x halo: the columns wrap in LDS).
+// Workgroup: one tile of 64 x 4 sites (all of the lattice's columns when nx <=
+// 64, then without an x halo: the columns wrap in LDS).  FP64 collisions are
+// taken on such lattices only.
 // One thread per site of the region, fixed for all steps: on rows of more
 // than 64 sites wavefront w < rows takes the 64 columns of region row w (the
 // same 64 sites as a wavefront of the one-step kernel, so that the
@@ -169,7 +170,7 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
     const SlotDesc* __restrict__ slots, const MultiShape M, const uint64_t* __restrict__ clock,
     uint32_t step_idx) {
   extern __shared__ __attribute__((aligned(16))) unsigned char multi_lds[];
-  const int K = M.K, nt = M.nt, ncw = M.ncw, H = K - 1, nx = M.nx, ny = M.ny;
+  const int K = M.K, ncw = M.ncw, H = K - 1, nx = M.nx, ny = M.ny;
   const uint32_t g = (uint32_t)xcd_tile(blockIdx.x, gridDim.x);
   const uint32_t slot = (uint32_t)(((uint64_t)g * M.gr_magic) >> M.gr_shift);
   const uint32_t lg = g - slot * (uint32_t)M.groups;
@@ -177,15 +178,15 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
   const int tx = (int)lg - gy * M.tiles_x;
   const SlotDesc& sd = slots[slot];
   const uint64_t t0 = sd.t0 + *clock + step_idx;
-  const bool full = nx <= kTileX;
-  const int x0 = tx * kTileX, y0 = gy * nt * kTileY;
-  const int TH = min(nt * kTileY, ny - y0);
+  const bool full = draws_apart<R>() || nx <= kTileX;
+  const int x0 = tx * kTileX, y0 = gy * kTileY;
+  const int TH = min(kTileY, ny - y0);
   const int W = min(kTileX, nx - x0);
   const int RH = TH + 2 * H;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
 
-  const int NR = nt * kTileY;
+  constexpr int NR = kTileY;
   const int nwaves = blockDim.x >> 6;
   // the wavefronts past the ncw colliding ones: the first nnw draw, the last
   // NR form the sums of a tile row each (some do both where both do not fit)
@@ -211,11 +212,6 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
         const int cw = (int)(((uint32_t)row * M.rpw_magic) >> 16);
         zslot = cw * 64 + (row - cw * rpw) * nx + colh - H;
       }
-    } else if (draws) {
-      row = wave - ncw + 1;
-      colh = lane + H;
-      valid = lane < W && row < RH - 1;
-      zslot = row * 64 + lane;
     } else if (wave < RH) {
       row = wave;
       colh = lane + H;
@@ -232,14 +228,14 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
   S* const pops = reinterpret_cast<S*>(multi_lds);
   // by the parity of the step: the pre-collision values of the tile rows
   // [2][row][value][64 sites]; the staging of the summing wavefronts; their
-  // results [2][row][kXtxVals]; the tiles' sums
+  // results [2][row][kXtxVals]; the tile's sums
   S* const raw = pops + (size_t)(NR + 2 * H) * 9 * kRS;
   unsigned char* const after = reinterpret_cast<unsigned char*>(raw + (size_t)2 * NR * 9 * kTileX);
   double* const red = reinterpret_cast<double*>(after + (size_t)NR * sample_wave_bytes<S>());
   double* const sums = red + (size_t)2 * NR * kXtxVals;
   // the draws, by the parity of the step: [2][value][colliding thread]
   using D = typename LdsDraw<S, R>::type;
-  D* const drawn = SAMPLE ? reinterpret_cast<D*>(sums + (size_t)nt * 64)
+  D* const drawn = SAMPLE ? reinterpret_cast<D*>(sums + 64)
                           : reinterpret_cast<D*>(pops + (size_t)(NR + 2 * H) * 9 * kRS);
   const int zplane = ncw * 64;
 
@@ -249,12 +245,9 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
   CollideConst<R> C;
   if constexpr (!draws_apart<R>()) C = collide_const<R>(sd);
 
-  // statistic `lane` of tile srow is kept by one thread of a summing wavefront
-  const bool keeps = SAMPLE && srow >= 0 && srow < nt && lane < kNStat &&
-                     y0 + srow * kTileY < ny && sd.sample_every > 0;
-  if (keeps)
-    sums[srow * 64 + lane] =
-        sd.partials[((size_t)(gy * nt + srow) * M.tiles_x + tx) * kNStat + lane];
+  // statistic `lane` is kept by one thread of the first summing wavefront
+  const bool keeps = SAMPLE && srow == 0 && lane < kNStat && sd.sample_every > 0;
+  if (keeps) sums[lane] = sd.partials[((size_t)gy * M.tiles_x + tx) * kNStat + lane];
   // sites past the end of a row count as zeros
   if (srow >= 0 && lane >= W)
     for (int q = 0; q < 2 * 9; ++q)
@@ -386,66 +379,59 @@ __global__ __launch_bounds__((multi_max_threads<R>())) void step_multi_kernel(
     if (was_due && keeps) {
       // rows past the lattice count as zeros; this result area is written
       // again two turns later, one barrier after these reads
-      const double* r = red + ((size_t)(s & 1) * NR + srow * kTileY) * kXtxVals + kXtxPos.pos[lane];
-      const int left = TH - srow * kTileY;
-      const double w0 = r[0], w1 = left > 1 ? r[kXtxVals] : 0.0;
-      const double w2 = left > 2 ? r[2 * kXtxVals] : 0.0, w3 = left > 3 ? r[3 * kXtxVals] : 0.0;
-      sums[srow * 64 + lane] += (w0 + w1) + (w2 + w3);
+      const double* r = red + (size_t)(s & 1) * NR * kXtxVals + kXtxPos.pos[lane];
+      const double w0 = r[0], w1 = TH > 1 ? r[kXtxVals] : 0.0;
+      const double w2 = TH > 2 ? r[2 * kXtxVals] : 0.0, w3 = TH > 3 ? r[3 * kXtxVals] : 0.0;
+      sums[lane] += (w0 + w1) + (w2 + w3);
     }
     was_due = due;
     to_sample = due ? (uint32_t)sd.sample_every - 1 : to_sample - 1;
   }
-  if (keeps)
-    sd.partials[((size_t)(gy * nt + srow) * M.tiles_x + tx) * kNStat + lane] =
-        sums[srow * 64 + lane];
+  if (keeps) sd.partials[((size_t)gy * M.tiles_x + tx) * kNStat + lane] = sums[lane];
 }
 
 // ------------------------------------------------------------- shapes
-static int colliding_waves(int nx, int K, int nt) {
-  const int H = K - 1, RH = nt * kTileY + 2 * H;
+static int colliding_waves(int nx, int K) {
+  const int H = K - 1, RH = kTileY + 2 * H;
   if (nx > kTileX) return RH + (2 * H * RH + 63) / 64;
   const int rpw = kTileX / nx;
   return (RH + rpw - 1) / rpw;
 }
-static int drawing_waves(int compute, int nx, int K, int nt) {
-  if (!(compute == 0 ? draws_apart<double>() : draws_apart<float>())) return 0;
-  const int RH = nt * kTileY + 2 * (K - 1), rpw = nx > kTileX ? 1 : kTileX / nx;
+static int drawing_waves(int compute, int nx, int K) {
+  if (nx > kTileX || !(compute == 0 ? draws_apart<double>() : draws_apart<float>())) return 0;
+  const int RH = kTileY + 2 * (K - 1), rpw = kTileX / nx;
   return (RH - 2 + rpw - 1) / rpw;
 }
 // All wavefronts of a workgroup: those that draw and those that sum are the
 // same ones where they would not fit side by side.
-int multi_waves(int compute, bool sample, int nx, int K, int nt) {
+int multi_waves(int compute, bool sample, int nx, int K) {
   const int most = (compute == 0 ? multi_max_threads<double>() : multi_max_threads<float>()) / 64;
-  const int nc = colliding_waves(nx, K, nt), nd = drawing_waves(compute, nx, K, nt);
+  const int nc = colliding_waves(nx, K), nd = drawing_waves(compute, nx, K), ns = kTileY;
   if (!sample) return nc + nd;
-  const int ns = nt * kTileY;
   return nc + (nc + nd + ns <= most ? nd + ns : std::max(nd, ns));
 }
 
-static size_t multi_lds_bytes(int storage, int compute, bool sample, int nx, int K, int nt) {
-  const int H = K - 1, RH = nt * kTileY + 2 * H;
-  const size_t es = storage == 0 ? 8 : 4, rows = (size_t)nt * kTileY;
+static size_t multi_lds_bytes(int storage, int compute, bool sample, int nx, int K) {
+  const int H = K - 1, RH = kTileY + 2 * H;
+  const size_t es = storage == 0 ? 8 : 4, rows = kTileY;
   size_t b = (size_t)RH * 9 * kRS * es;
   if (sample)
     b += rows * (2 * 9 * kTileX * es + 2 * kXtxVals * sizeof(double) +
                  (storage == 0 ? sample_wave_bytes<double>() : sample_wave_bytes<float>())) +
-         (size_t)nt * 64 * sizeof(double);
-  if (drawing_waves(compute, nx, K, nt))
+         64 * sizeof(double);
+  if (drawing_waves(compute, nx, K))
     b += 2 * (storage != compute ? 6 * sizeof(float) : 9 * es) * 64 *
-         (size_t)colliding_waves(nx, K, nt);
+         (size_t)colliding_waves(nx, K);
   return b;
 }
 
-bool multi_fits(int storage, int compute, bool sample, int nx, int K, int nt, size_t max_lds) {
-  if (K < 2 || K > kMultiMaxSteps || (K & 1) || nt < 1) return false;
-  if (nx > kTileX) {
-    // halo columns: as many as the row stride holds; the drawing wavefronts
-    // take none, which the second step of more than two would need
-    if (K - 1 > kMultiMaxHalo || (drawing_waves(compute, nx, K, nt) && K > 2)) return false;
-  }
+bool multi_fits(int storage, int compute, bool sample, int nx, int K, size_t max_lds) {
+  if (K < 2 || K > kMultiMaxSteps || (K & 1)) return false;
+  // halo columns: as many as the row stride holds; FP64 collisions take none
+  if (nx > kTileX && (K - 1 > kMultiMaxHalo || compute == 0)) return false;
   const int most = compute == 0 ? multi_max_threads<double>() : multi_max_threads<float>();
-  return 64 * multi_waves(compute, sample, nx, K, nt) <= most &&
-         multi_lds_bytes(storage, compute, sample, nx, K, nt) <= max_lds;
+  return 64 * multi_waves(compute, sample, nx, K) <= most &&
+         multi_lds_bytes(storage, compute, sample, nx, K) <= max_lds;
 }
 
 // Launches above 64 KiB of LDS have to be allowed, kernel by kernel.
@@ -464,7 +450,7 @@ static hipError_t allow_lds(int basis, int bytes) {
 }
 
 hipError_t multi_prepare(int storage, int compute, int basis, int nx, int K, size_t max_lds) {
-  if (multi_lds_bytes(storage, compute, true, nx, K, 1) <= 65536) return hipSuccess;
+  if (multi_lds_bytes(storage, compute, true, nx, K) <= 65536) return hipSuccess;
   if (storage == 0) return allow_lds<double, double>(basis, (int)max_lds);
   if (compute == 0) return allow_lds<float, double>(basis, (int)max_lds);
   return allow_lds<float, float>(basis, (int)max_lds);
@@ -472,7 +458,7 @@ hipError_t multi_prepare(int storage, int compute, int basis, int nx, int K, siz
 
 template <typename S, typename R, int BASIS>
 static hipError_t launch_multi_t(bool sample, const SlotDesc* d_slots, int nslots, int nx, int ny,
-                                 int K, int nt, int flip, const uint64_t* clk, uint32_t step_idx,
+                                 int K, int flip, const uint64_t* clk, uint32_t step_idx,
                                  hipStream_t st) {
   constexpr int storage = sizeof(S) == 8 ? 0 : 1, compute = sizeof(R) == 8 ? 0 : 1;
   MultiShape M{};
@@ -480,19 +466,18 @@ static hipError_t launch_multi_t(bool sample, const SlotDesc* d_slots, int nslot
   M.ny = ny;
   M.tiles_x = (nx + kTileX - 1) / kTileX;
   M.pitch = (uint32_t)M.tiles_x * kTileX;
-  M.groups = M.tiles_x * ((ny + nt * kTileY - 1) / (nt * kTileY));
+  M.groups = M.tiles_x * ((ny + kTileY - 1) / kTileY);
   magic_div((uint32_t)M.groups, &M.gr_magic, &M.gr_shift);
   magic_div((uint32_t)M.tiles_x, &M.tx_magic, &M.tx_shift);
   M.K = K;
-  M.nt = nt;
-  M.ncw = colliding_waves(nx, K, nt);
-  M.nnw = drawing_waves(compute, nx, K, nt);
+  M.ncw = colliding_waves(nx, K);
+  M.nnw = drawing_waves(compute, nx, K);
   M.rpw = nx > kTileX ? 1 : kTileX / nx;
   M.nx_magic = 65536u / (uint32_t)nx + 1;
   M.rpw_magic = 65536u / (uint32_t)M.rpw + 1;
   M.flip = flip;
-  const dim3 grid((unsigned)M.groups * nslots), b(64 * multi_waves(compute, sample, nx, K, nt));
-  const size_t lds = multi_lds_bytes(storage, compute, sample, nx, K, nt);
+  const dim3 grid((unsigned)M.groups * nslots), b(64 * multi_waves(compute, sample, nx, K));
+  const size_t lds = multi_lds_bytes(storage, compute, sample, nx, K);
   if (sample)
     hipLaunchKernelGGL((step_multi_kernel<S, R, BASIS, true>), grid, b, lds, st, d_slots, M, clk,
                        step_idx);
@@ -504,34 +489,33 @@ static hipError_t launch_multi_t(bool sample, const SlotDesc* d_slots, int nslot
 
 template <typename S, typename R>
 static hipError_t launch_multi_b(int basis, bool sample, const SlotDesc* d_slots, int nslots,
-                                 int nx, int ny, int K, int nt, int flip, const uint64_t* clk,
+                                 int nx, int ny, int K, int flip, const uint64_t* clk,
                                  uint32_t k, hipStream_t st) {
   switch (basis) {
     case kBasisFnormLocal:
-      return launch_multi_t<S, R, kBasisFnormLocal>(sample, d_slots, nslots, nx, ny, K, nt, flip,
+      return launch_multi_t<S, R, kBasisFnormLocal>(sample, d_slots, nslots, nx, ny, K, flip,
                                                     clk, k, st);
     case kBasisHermite:
-      return launch_multi_t<S, R, kBasisHermite>(sample, d_slots, nslots, nx, ny, K, nt, flip,
+      return launch_multi_t<S, R, kBasisHermite>(sample, d_slots, nslots, nx, ny, K, flip,
                                                  clk, k, st);
     case kBasisFnormLut:
-      return launch_multi_t<S, R, kBasisFnormLut>(sample, d_slots, nslots, nx, ny, K, nt, flip,
+      return launch_multi_t<S, R, kBasisFnormLut>(sample, d_slots, nslots, nx, ny, K, flip,
                                                   clk, k, st);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_step_multi(int storage, int compute, int basis, bool sample,
-                             const SlotDesc* d_slots, int nslots, int nx, int ny, int K, int nt,
-                             int flip, const uint64_t* d_clock, uint32_t step_idx,
-                             hipStream_t st) {
+                             const SlotDesc* d_slots, int nslots, int nx, int ny, int K, int flip,
+                             const uint64_t* d_clock, uint32_t step_idx, hipStream_t st) {
   if (nslots <= 0) return hipSuccess;
   if (storage == 0)
-    return launch_multi_b<double, double>(basis, sample, d_slots, nslots, nx, ny, K, nt, flip,
+    return launch_multi_b<double, double>(basis, sample, d_slots, nslots, nx, ny, K, flip,
                                           d_clock, step_idx, st);
   if (compute == 0)
-    return launch_multi_b<float, double>(basis, sample, d_slots, nslots, nx, ny, K, nt, flip,
+    return launch_multi_b<float, double>(basis, sample, d_slots, nslots, nx, ny, K, flip,
                                          d_clock, step_idx, st);
-  return launch_multi_b<float, float>(basis, sample, d_slots, nslots, nx, ny, K, nt, flip, d_clock,
+  return launch_multi_b<float, float>(basis, sample, d_slots, nslots, nx, ny, K, flip, d_clock,
                                       step_idx, st);
 }
 
