@@ -272,8 +272,10 @@ int flb_lattice_population_buffer(flb_lattice* L, void** dev, size_t* bytes, uin
  * launches (one per step, or per several steps as below; FP32 replicas with
  * |u0| > 0.25, which need the FP64 collision, form their own); chunks of
  * steps are replayed from a captured hipGraph, in which two halves of many
- * replicas advance side by side.  Replica results are bit-identical to
- * running each alone. */
+ * replicas advance side by side while nothing else that the library has
+ * enqueued on the device is unfinished (as far as its own waits tell), or
+ * where their populations outgrow the last-level cache.  Replica results are
+ * bit-identical to running each alone. */
 typedef struct flb_ensemble flb_ensemble;
 int flb_ensemble_create(const flb_params* per_replica, int32_t n, void* hip_stream,
                         flb_ensemble** out);
@@ -343,10 +345,8 @@ int flb_lattice_autotune(flb_lattice* L, int32_t reps, flb_launch_config* result
 int flb_ensemble_autotune(flb_ensemble* E, int32_t reps, flb_launch_config* results,
                           int32_t max_results, int32_t* n_results);
 /* Force a shape, and one step per launch, of all replicas, until the next
- * autotune: also the choice for several large ensembles stepped side by side
- * on streams of their own, which overlap by themselves (FLB_E_ARG
- * for tiles_per_block not in {1, 2, 4} or a negative grid_blocks or one that
- * is not a multiple of 8). */
+ * autotune (FLB_E_ARG for tiles_per_block not in {1, 2, 4} or a negative
+ * grid_blocks or one that is not a multiple of 8). */
 int flb_lattice_set_launch(flb_lattice* L, const flb_launch_config* c);
 int flb_ensemble_set_launch(flb_ensemble* E, const flb_launch_config* c);
 int flb_lattice_get_launch(flb_lattice* L, flb_launch_config* c);
@@ -416,8 +416,8 @@ void flb3_lattice_destroy(flb3_lattice* L);
  * Continuous batching of simulation requests of mixed size, temperature and
  * background velocity.  Requests wait in FIFO order; one is admitted as soon
  * as a slot is free and its device footprint fits the memory budget; all
- * admitted requests advance together, one batched launch per step and half
- * of the requests (the halves side by side on two streams), in
+ * admitted requests advance together, one batched launch per step, or two
+ * halves of the requests side by side on two streams (as an ensemble's), in
  * chunks of `chunk_steps`; finished requests leave at chunk boundaries and
  * free their slot and memory for the next.  A request's result equals the
  * result of running it alone (noise keyed by its own seed, step and site;

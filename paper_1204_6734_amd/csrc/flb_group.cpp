@@ -482,10 +482,13 @@ void Group::plan_multi(int cus) {
 // Rows a wavefront of step_march_kernel takes, 0 where one step per launch is
 // the better one.  Two steps per pass over memory halve the traffic and cost
 // (64/62)(1 + 1/H) of the arithmetic, so they pay where the FP32 arithmetic is
-// the smaller part: never in FP64, in the Hermite basis where the populations
-// exceed the 32 MiB of the XCDs' L2 caches, in the others (twice the
-// arithmetic) where they exceed the 256 MiB last-level cache.  us a step, one
-// step per launch -> this kernel:
+// the smaller part: in the Hermite basis where the populations exceed the 32 MiB
+// of the XCDs' L2 caches, in the others (twice the arithmetic) where they exceed
+// the 256 MiB last-level cache.  Not in FP64: f-norm lattices run 8 % faster in
+// the cache than beyond it (40.9 GLUPS at 1792^2, 220 MiB, 37.4-37.6 from 3072^2
+// on; mixed relaxation times 39.4 and 36.2-36.5), which the 6.5 % of halo sites
+// would take; the Hermite basis was not tried.  us a step, one step per launch ->
+// this kernel:
 //   f-norm   2560^2 (225 MiB) 71 -> 78, 2003x4001 (275) 95.5 -> 96.4, 2900^2
 //            (289) 105 -> 100, 3072^2 (324) 116 -> 107, 8192^2 845 -> 694
 //   Hermite  1003x601 (21) 7.7 -> 8.1, 1024^2 (36) 13.8 -> 11.3, 2048^2 43.8 ->

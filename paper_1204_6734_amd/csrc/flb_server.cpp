@@ -6,7 +6,8 @@
 // the head request's device footprint fits the memory budget (a first-fit
 // arena carved from one allocation of the budget).  All admitted requests
 // then advance together for `chunk_steps` steps: one batched step launch
-// per step and compute precision covers every active lattice; a request that
+// per step and compute precision, or one for each of two halves on two streams,
+// covers every active lattice; a request that
 // reaches its step count stops updating inside the chunk.  A request runs
 // on its own clock (t = t0 + device clock), with noise keyed by its own
 // seed, step and site and its correlator sums reduced per request in a
