@@ -649,11 +649,12 @@ hipError_t Group::launch_pass(uint32_t k, uint64_t tt, int K, int flip) {
 // 158).
 int Group::graph_branches(bool alone) const {
   if (P.size() < 2 || d_skacc || forced_launch) return 1;
+  if (!two_branches(compute, total_tiles, alone)) return 1;
   const double share = pass_share((uint64_t)graph_chunk);
   if (share > 0 && (!march_rows || basis == FLB_BASIS_HERMITE || share >= 0.5)) return 1;
   for (auto& h : hdesc)
     if (h.ntiles != hdesc[0].ntiles) return 1;
-  return two_branches(compute, total_tiles, alone) ? 2 : 1;
+  return 2;
 }
 
 int Group::abandon_capture(hipError_t e) {
