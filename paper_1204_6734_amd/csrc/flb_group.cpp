@@ -161,6 +161,7 @@ int Group::init(const flb_params* ps, int n, void* stream, void* dev_buf, size_t
       if (second) e = hipMalloc(&dev, both.used + 256);
       if (second && e != hipSuccess) {
         (void)hipGetLastError();
+        second_bytes.give();
         second = false;  // one step per launch needs less
       }
       if (second) need_bytes = both.used + 256;
@@ -514,17 +515,22 @@ int Group::plan_march(int cus) const {
   return waves >= (hermite ? 16.0 : 64.0) * cus ? rows : rows / 2;
 }
 
-// Whether a second population buffer of this size is taken: where seven eighths
-// of the device's memory stay free beside both buffers (16384 x 16384 takes twice
-// 9.7 of 288 GB).  A program that fills the memory, with one lattice or with
-// thousands of small ones, gives at most a sixteenth of it to second buffers.
-bool Group::take_second(size_t bytes) const {
+// Whether a second population buffer of this size is taken: where it and the
+// process's others hold at most a sixteenth of the device's memory, and it at
+// most a sixteenth of what the first leaves free.  A program that fills the
+// memory, with one lattice or with thousands of small ones, holds at least
+// fifteen sixteenths of what it would; what else is in the memory takes the
+// launches of several steps from a small lattice only where next to nothing is
+// left (16384 x 16384 takes twice 9.7 of 288 GB, while 155 stay free beside the
+// first).
+bool Group::take_second(size_t bytes) {
   size_t freeb = 0, total = 0;
   if (hipMemGetInfo(&freeb, &total) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return (double)freeb - (double)need_bytes - (double)bytes >= 0.875 * (double)total;
+  if (freeb < need_bytes || bytes > (freeb - need_bytes) / 16) return false;
+  return second_bytes.take(device, bytes, total / 16);
 }
 
 // Largest launch from the even time tt within `lim` steps that holds no

@@ -75,6 +75,7 @@ struct Group {
   // per launch) and, without and with correlator sums, the numbers of steps
   // that launches take
   char* pop2 = nullptr;
+  SecondBytes second_bytes;  // given back after the memory
   bool multi_takes[2][kMultiMaxSteps + 1] = {{false}};
   int multi_max = 0;
   std::vector<uint64_t> sample_intervals;  // the members' different ones
@@ -126,7 +127,7 @@ struct Group {
   double pass_share(uint64_t steps = 0) const;
   bool passes_pay() const;
   int sk_interval() const { return P.size() == 1 ? P[0].sk_every : 0; }
-  bool take_second(size_t bytes) const;
+  bool take_second(size_t bytes);
   int pass_steps(uint64_t tt, uint64_t lim) const;
   bool pass_samples(uint64_t tt, int K) const;
   void pass_pair(uint64_t tt, uint64_t left, bool closes, int* ka, int* kb) const;

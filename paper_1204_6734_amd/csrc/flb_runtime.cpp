@@ -45,8 +45,9 @@ int hip_fail(hipError_t e, const char* what) {
 
 // ---------------------------------------------------------------- at work
 namespace {
-constexpr int kMaxDevices = 64;  // above: never anything else at work
+constexpr int kMaxDevices = 64;  // above: never anything else at work, no second buffers
 std::atomic<int> g_at_work[kMaxDevices];
+std::atomic<size_t> g_second_bytes[kMaxDevices];
 }  // namespace
 
 void AtWork::begin(int device) {
@@ -64,6 +65,24 @@ void AtWork::end() {
 bool AtWork::others(int device) const {
   if (device < 0 || device >= kMaxDevices) return false;
   return g_at_work[device].load(std::memory_order_relaxed) > (on_ == device ? 1 : 0);
+}
+
+bool SecondBytes::take(int device, size_t bytes, size_t most) {
+  give();
+  if (device < 0 || device >= kMaxDevices || bytes > most) return false;
+  std::atomic<size_t>& sum = g_second_bytes[device];
+  size_t was = sum.load(std::memory_order_relaxed);
+  do {
+    if (was > most - bytes) return false;
+  } while (!sum.compare_exchange_weak(was, was + bytes, std::memory_order_relaxed));
+  device_ = device;
+  bytes_ = bytes;
+  return true;
+}
+
+void SecondBytes::give() {
+  if (device_ >= 0) g_second_bytes[device_].fetch_sub(bytes_, std::memory_order_relaxed);
+  device_ = -1;
 }
 
 // ---------------------------------------------------------------- readouts

@@ -80,6 +80,22 @@ class AtWork {
   int on_ = -1;  // the device, while at work
 };
 
+// A second population buffer's bytes, counted over the process by device while
+// it lives; refused where the sum would exceed `most`.
+class SecondBytes {
+ public:
+  SecondBytes() = default;
+  ~SecondBytes() { give(); }
+  SecondBytes(const SecondBytes&) = delete;
+  SecondBytes& operator=(const SecondBytes&) = delete;
+  bool take(int device, size_t bytes, size_t most);
+  void give();
+
+ private:
+  int device_ = -1;  // while bytes are taken
+  size_t bytes_ = 0;
+};
+
 // Readouts to caller-owned host memory go through page-locked staging: a copy
 // of 14 MB straight into pageable memory takes 0.86 ms, through it 0.45, and
 // every small piece 10 to 15 us.  The staging is the process's, held while any

@@ -245,6 +245,36 @@ assert sum(int(x.split()[1]) > one + one // 4 for x in log("M")) > 5
 """)
 
 
+def test_second_buffers_beside_other_memory(program):
+    """Memory that something else holds does not take the launches of several
+    steps from a lattice; the process's second buffers together hold a sixteenth
+    at most, which those of destroyed lattices no longer count in."""
+    program("""
+total = 288 << 30
+other = C.c_void_p()
+fake.hipMalloc.argtypes = [C.c_void_p, C.c_size_t]
+assert fake.hipMalloc(C.byref(other), int(0.9 * total)) == 0
+
+def several(p):
+    L = F.Lattice(p)
+    L.step(4)
+    return L.pass_steps() == 4, L
+
+small, large = P(64, 64), P(8192, 8192)  # the larger one: 2.25 GiB, 28.8 are free
+assert several(small)[0]
+assert not several(large)[0]
+fake.hipFree.argtypes = [C.c_void_p]
+fake.hipFree(other)
+for _ in range(2):  # eight of 2.25 GiB are a sixteenth of 288
+    held = [several(large) for _ in range(9)]
+    assert [h[0] for h in held] == [True] * 8 + [False], [h[0] for h in held]
+    assert not several(small)[0]
+    held.pop(0)
+    assert several(small)[0]
+    del held
+""")
+
+
 @pytest.mark.parametrize("launch", [1, 2, 5])
 def test_a_failed_chunk_leaves_nothing_on_the_second_stream(program, launch):
     """The next chunk writes the tables that the second stream's launches of
