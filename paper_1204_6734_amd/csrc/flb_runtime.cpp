@@ -87,11 +87,15 @@ void SecondBytes::give() {
 
 // ---------------------------------------------------------------- readouts
 namespace {
-// Two areas: a small one for correlators, flags and the fields of small
+// Two areas: a small one for flags, correlators and the fields of small
 // lattices, and two halves for larger readouts.  Page-locked memory is slow to
-// allocate (the large area costs what it saves on one readout of 14 MB), so
-// the large one is allocated by the second readout that wants it.
-constexpr size_t kSmallBytes = (size_t)256 << 10, kStageBytes = (size_t)8 << 20;
+// allocate (the large area costs what it saves on one readout of 14 MB; 25 us
+// for the small one, whatever its size up to 2 MiB), so the large one is
+// allocated by the second readout that wants it.  The small one holds the
+// correlators of a lattice whole, with all their time blocks (1024 of 209
+// statistics, 1.7 MB); fields above 256 KiB are faster polled for in halves.
+constexpr size_t kSmallArea = (size_t)2 << 20, kSmallFields = (size_t)256 << 10;
+constexpr size_t kStageBytes = (size_t)8 << 20;
 std::mutex g_stage_count_mu, g_small_mu, g_stage_mu;  // the count; the areas
 int g_stage_users = 0;
 bool g_stage_wanted = false;
@@ -126,10 +130,14 @@ Staging::~Staging() {
 hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st, bool behind_steps) {
   size_t total = 0;
   for (int i = 0; i < n; ++i) total += (pieces[i].bytes + 15) & ~(size_t)15;
-  const bool small = total <= kSmallBytes;
-  // the halves are polled for and hold the large area: steps enqueued before
-  // them are waited for first, asleep and without it.  A small readout waits
-  // for everything once, holding only its own area.
+  // A small readout waits for everything once, holding only its own area.  The
+  // halves are polled for and hold the large one: steps enqueued before them
+  // are waited for first, asleep and without it.  The second wait costs 17 to 30
+  // us (200 steps of 256x94 and their correlators 904 -> 921 us, 40 of 14x113x13
+  // D3Q19 492 -> 522), so what waits for steps takes the small area if it fits:
+  // there one wait takes what polling did (700 blocks 885 and 887 us; D3Q19,
+  // 600 blocks, 599 and 594).
+  const bool small = total <= (behind_steps ? kSmallArea : kSmallFields);
   if (!small && behind_steps) {
     const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
@@ -138,7 +146,7 @@ hipError_t copy_out(const HostPiece* pieces, int n, hipStream_t st, bool behind_
   char* area = nullptr;
   if (lk.owns_lock()) {
     if (small) {
-      area = locked_area(g_small, kSmallBytes);
+      area = locked_area(g_small, kSmallArea);
     } else {
       if (g_stage_wanted) area = locked_area(g_stage, 2 * kStageBytes);
       g_stage_wanted = true;

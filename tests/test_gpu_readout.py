@@ -97,3 +97,25 @@ def test_readouts_from_several_threads(flb):
     for t in ts:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("lattice,blocks", [("d2q9", 500), ("d2q9", 700), ("d2q9", 1023),
+                                            ("d3q19", 150), ("d3q19", 600), ("d3q19", 1023)])
+def test_correlators_behind_steps_equal_those_after_a_wait(flb, lattice, blocks):
+    """Closed blocks below and above 256 KiB, read while their steps run."""
+    def make():
+        if lattice == "d2q9":
+            return flb.Lattice(flb.make_params(16, 12, kT=1e-4, seed=3, init=flb.INIT_THERMAL,
+                                               sample_every=1, block_steps=1))
+        return flb.Lattice3(flb.make_params3(8, 5, 4, kT=1e-4, seed=3, sample_every=1,
+                                             block_steps=1))
+
+    a, b = make(), make()
+    for _ in range(3):
+        a.step(blocks // 3)
+        b.step(blocks // 3)
+        b.sync()
+        got, want = a.covariance(), b.covariance()
+        assert got["nblocks"] == want["nblocks"] > 0
+        for k in want:
+            np.testing.assert_array_equal(got[k], want[k])
