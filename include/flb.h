@@ -317,10 +317,10 @@ void flb_ensemble_destroy(flb_ensemble* E);
  * with the populations in the workgroups' LDS; and FP32 ones larger than the caches
  * (300 MiB of populations, 32 MiB in the Hermite basis), two steps per pass
  * over memory.  They write to a second population buffer, which is taken only
- * where the sampling leaves room for such launches, where the process's second
- * buffers hold at most a sixteenth of the device's memory, and where it is at
- * most a sixteenth of what the first leaves free; otherwise, and after
- * flb_*_set_launch, each launch is one step.  Results are the same bit for bit.
+ * where the sampling leaves room for such launches, and where the process's
+ * second buffers on the device then hold at most a fifteenth of what stays
+ * free; otherwise, and after flb_*_set_launch, each launch is one step.
+ * Results are the same bit for bit.
  * A new lattice or ensemble starts with {1, 0}, or with the shape an earlier
  * autotune in this process chose for the same device, precision, basis and
  * tile count. */

@@ -515,22 +515,21 @@ int Group::plan_march(int cus) const {
   return waves >= (hermite ? 16.0 : 64.0) * cus ? rows : rows / 2;
 }
 
-// Whether a second population buffer of this size is taken: where it and the
-// process's others hold at most a sixteenth of the device's memory, and it at
-// most a sixteenth of what the first leaves free.  A program that fills the
-// memory, with one lattice or with thousands of small ones, holds at least
-// fifteen sixteenths of what it would; what else is in the memory takes the
-// launches of several steps from a small lattice only where next to nothing is
-// left (16384 x 16384 takes twice 9.7 of 288 GB, while 155 stay free beside the
-// first).
+// Whether a second population buffer of this size is taken: where all of the
+// process's on the device then hold at most a fifteenth of what stays free.  So a
+// program that fills the memory, with one lattice or with thousands of small ones,
+// holds at least fifteen sixteenths of what it would, also where others hold most
+// of it; and memory in use takes the launches of several steps from a lattice only
+// where its buffer would be a large part of the rest (16384 x 16384 takes twice 9.7
+// of 288 GB).
 bool Group::take_second(size_t bytes) {
   size_t freeb = 0, total = 0;
   if (hipMemGetInfo(&freeb, &total) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  if (freeb < need_bytes || bytes > (freeb - need_bytes) / 16) return false;
-  return second_bytes.take(device, bytes, total / 16);
+  if (freeb < need_bytes + bytes) return false;
+  return second_bytes.take(device, bytes, (freeb - need_bytes - bytes) / 15);
 }
 
 // Largest launch from the even time tt within `lim` steps that holds no

@@ -228,8 +228,8 @@ assert grids == [(n - 20) * want[0], 20 * want[0], (n - 20) * want[1], 20 * want
 
 
 def test_a_full_device_holds_nearly_as_many_small_lattices(program):
-    """Second buffers stop being taken once an eighth of the memory is in use:
-    a program that fills the device gives them a sixteenth of it at most."""
+    """A program that fills the device gives second buffers a sixteenth of it at
+    most."""
     program("""
 one = F.Lattice.bytes_needed(P(64, 64))  # a lattice that takes a second buffer
 total = 400 * one
@@ -247,31 +247,40 @@ assert sum(int(x.split()[1]) > one + one // 4 for x in log("M")) > 5
 
 def test_second_buffers_beside_other_memory(program):
     """Memory that something else holds does not take the launches of several
-    steps from a lattice; the process's second buffers together hold a sixteenth
-    at most, which those of destroyed lattices no longer count in."""
+    steps from a lattice, and lattices that fill the rest of it are nearly as many
+    as without second buffers; those of destroyed lattices no longer count."""
     program("""
 total = 288 << 30
 other = C.c_void_p()
 fake.hipMalloc.argtypes = [C.c_void_p, C.c_size_t]
-assert fake.hipMalloc(C.byref(other), int(0.9 * total)) == 0
+fake.hipFree.argtypes = [C.c_void_p]
+small, large = P(64, 64), P(8192, 8192)  # the larger one: 2.25 GiB
 
 def several(p):
     L = F.Lattice(p)
     L.step(4)
     return L.pass_steps() == 4, L
 
-small, large = P(64, 64), P(8192, 8192)  # the larger one: 2.25 GiB, 28.8 are free
+assert fake.hipMalloc(C.byref(other), int(0.9 * total)) == 0
 assert several(small)[0]
-assert not several(large)[0]
-fake.hipFree.argtypes = [C.c_void_p]
+assert not several(large)[0]  # of 28.8 GiB
 fake.hipFree(other)
-for _ in range(2):  # eight of 2.25 GiB are a sixteenth of 288
+for _ in range(2):
     held = [several(large) for _ in range(9)]
-    assert [h[0] for h in held] == [True] * 8 + [False], [h[0] for h in held]
-    assert not several(small)[0]
+    assert [h[0] for h in held] == [True] * 7 + [False] * 2, [h[0] for h in held]
     held.pop(0)
-    assert several(small)[0]
+    assert several(large)[0]
     del held
+
+one = F.Lattice.bytes_needed(small)
+assert fake.hipMalloc(C.byref(other), total - 400 * one) == 0
+held = []
+try:
+    while True:
+        held.append(F.Lattice(small))
+except F.FlbError as e:
+    assert e.code == F.E_OOM
+assert len(held) >= 400 * 15 // 16, len(held)
 """)
 
 
